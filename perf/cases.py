@@ -1,0 +1,770 @@
+"""Performance cases of libpmp: what a program that drives the library has it do.
+
+A case is a dict of plain values.  ``prepare`` makes what such a program holds on
+the GPU before the call (mesh context, gas state, particle arrays, buffer and,
+where the case replays one, the captured graph), ``run`` is one pass through the
+C ABI of ``include/pmp.h`` as loaded by the package's binding, ``work`` the bytes
+the pass cannot do without and ``exact`` the same result in plain 64-bit torch
+arithmetic.
+
+Kinds of pass (``call``):
+
+* ``step``    one eager ``pmp_step``;
+* ``graph``   one replay of a captured step (``pmp_graph_launch``);
+* ``calls``   the separate entry points ``pmp_deposit``, ``pmp_ghost_fold``,
+              ``pmp_sink_update`` (with sinks) and ``pmp_apply``; the folded
+              buffer is a result too;
+* ``snr``     ``pmp_deposit``, ``pmp_deposit_snr``, ``pmp_ghost_fold``, ``pmp_apply``;
+* ``create``  ``pmp_step`` with sinks, then ``pmp_sink_create``.
+
+A case with ``tile_x`` 0 runs on the tuning a new context starts with; the others
+set a tuning as a program does that saved what the tuner found for its shape.
+"""
+import ctypes as C
+import math
+
+import numpy as np
+import torch
+
+from paper_2509_18261_amd import binding as B
+from paper_2509_18261_amd import workloads as W
+
+DEV = "cuda"
+ACC_DTYPE = {"f32": torch.float32, "f64": torch.float64, "f64r": torch.float64,
+             "fix64": torch.int64}
+STATE_DTYPE = {"f32": torch.float32, "f64": torch.float64}
+
+BASE = {
+    "call": "step", "nx": 64, "ny": 64, "nz": 64,
+    "nb": 1, "emin": 8, "emax": 64, "layout": 5,   # nb > 1: nb^3 boxes, edges drawn from `layout`
+    "ghost": 4, "acc": "f64", "state": "f64", "all_channels": False, "eint_mode": 0,
+    "n_cic": 0, "n_sn": 0, "r_sn": 3.0, "spread": "uniform",
+    "n_sink": 0, "bondi": False, "r_k": 4.0, "rho_tr": math.inf,
+    "n_snr": 0, "sub": 4, "max_new": 0,
+    "tile_x": 0, "tile_yz": 4, "tile_block": 256, "fuse": 2, "chunk_cic": 16384,
+    "chunk_sn": 2048, "count_lanes": 4,
+}
+
+
+def _case(name, **kw):
+    return {"name": name, **BASE, **kw}
+
+
+def listed():
+    return [
+        # the smallest grid patch of a simulation: latency and launches (default tuning, fixed point)
+        _case("step_32_fix64", nx=32, ny=32, nz=32, ghost=2, acc="fix64", n_cic=8, n_sn=8,
+              r_sn=2.0),
+        # an odd mid-size box as a single-GPU test run has it, default tuning, FP32
+        _case("step_101_f32", nx=101, ny=83, nz=67, acc="f32", state="f32", n_cic=33001,
+              n_sn=3301, r_sn=4.0),
+        # the ordinary box: 256^3, uniform CIC mass and supernovae, FP64
+        _case("step_256_f64", nx=256, ny=256, nz=256, n_cic=1_000_000, n_sn=100_000, r_sn=4.0,
+              tile_x=64),
+        # the governing configuration: 512^3, half the particles in clumps, FP64
+        _case("step_512_f64", nx=512, ny=512, nz=512, n_cic=3_636_364, n_sn=363_636, r_sn=3.0,
+              spread="clumps", tile_x=128),
+        # the same with bit-reproducible fixed-point sums over an FP32 state
+        _case("step_512_fix64", nx=512, ny=512, nz=512, n_cic=3_636_364, n_sn=363_636, r_sn=3.0,
+              spread="clumps", acc="fix64", state="f32", tile_x=64, count_lanes=1),
+        # accreting sinks in the core of a cluster
+        _case("sinks_256_f64", nx=256, ny=256, nz=256, n_cic=1_000_000, spread="plummer",
+              n_sink=256, tile_x=16, tile_yz=8),
+        # an adaptive-mesh level of 4096 uneven boxes, replayed from its graph
+        _case("boxes_4096_f32", call="graph", nb=16, ghost=2, acc="f32", state="f32",
+              n_cic=7_272_727, n_sn=727_273, r_sn=2.0, spread="clumps", tile_x=32, tile_block=128,
+              count_lanes=1),
+        # a smaller level with Bondi-Hoyle sinks across its boxes
+        _case("boxes_512_bondi_f64", nb=8, ghost=2, layout=6, n_cic=909_091, n_sn=90_909,
+              r_sn=2.0, spread="clumps", n_sink=128, bondi=True, r_k=2.0, tile_x=32,
+              tile_block=128),
+        # the separate calls of a code that keeps the buffer (its own exchange or analysis in
+        # between), default tuning
+        _case("calls_256_f64", call="calls", nx=256, ny=256, nz=256, n_cic=1_000_000,
+              n_sn=100_000, r_sn=4.0, n_sink=256, all_channels=True),
+        # the paper's reproducibility mode (error bounds and truncation), default tuning
+        _case("repro_256_f64", nx=256, ny=256, nz=256, acc="f64r", n_cic=1_000_000,
+              n_sn=100_000, r_sn=4.0),
+        # resolved supernova remnants with the TIGRESS variant over gas of three densities
+        _case("snr_256_f64", call="snr", nx=256, ny=256, nz=256, n_cic=100_000, n_snr=20_000,
+              r_k=3.0, all_channels=True),
+        # a star-forming core: the step, then the search for new sinks
+        _case("create_256_f64", call="create", nx=256, ny=256, nz=256, n_cic=1_000_000,
+              spread="plummer", n_sink=256, rho_tr=100.0, max_new=4096, tile_x=16, tile_yz=8),
+    ]
+
+
+def _log_int(rng, lo, hi):
+    return int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+
+
+def draw(rng):
+    c = dict(BASE)
+    kind = rng.choice(["box", "box", "box", "sinks", "boxes", "boxes", "box_sinks", "calls",
+                       "repro", "snr", "create"])
+    acc, state = rng.choice([("f64", "f64"), ("f64", "f64"), ("f32", "f32"), ("fix64", "f32"),
+                             ("fix64", "f64")])
+    c["acc"], c["state"] = acc, state
+    c["eint_mode"] = rng.choice([0, 0, 0, 1])
+    if kind in ("boxes", "box_sinks"):
+        c["nb"] = rng.randint(2, 11)
+        c["emax"] = rng.randint(16, 64)
+        c["layout"] = rng.randint(1, 10 ** 6)
+        c["ghost"] = rng.randint(2, 4)
+        c["call"] = rng.choice(["step", "graph"])
+        cells = int(np.prod([sum(e) for e in _edges(c)]))
+    else:
+        top = 320 if kind == "box" else 256
+        c["nx"], c["ny"], c["nz"] = (_log_int(rng, 20, top) for _ in range(3))
+        c["ghost"] = rng.randint(3, 5)
+        cells = c["nx"] * c["ny"] * c["nz"]
+    # particles per cell as in the listed cases, give or take a factor of three
+    c["n_cic"] = max(1, int(cells * _log_int(rng, 8000, 120000) / 1e6))
+    c["spread"] = rng.choice(["uniform", "clumps", "plummer"])
+    c["n_cic"] = min(c["n_cic"], 1_000_000 if c["spread"] == "plummer" else 2_000_000)
+    if kind in ("box", "boxes", "calls", "repro") or rng.random() < 0.3:
+        c["n_sn"] = max(1, int(c["n_cic"] * rng.uniform(0.03, 0.15)))
+        c["n_sn"] = min(c["n_sn"], 10_000 if c["spread"] == "plummer" else 150_000)
+        c["r_sn"] = rng.choice([1.5, 2.0, 2.5, 3.0, 3.5, 4.0])
+        c["r_sn"] = min(c["r_sn"], float(c["ghost"]))
+    if kind in ("sinks", "box_sinks", "create") or (kind == "calls" and rng.random() < 0.5):
+        c["n_sink"] = _log_int(rng, 1, 400)
+        c["bondi"] = rng.random() < 0.4
+        c["r_k"] = float(rng.randint(2, c["ghost"]))
+    if kind == "calls":
+        c["call"], c["all_channels"] = "calls", rng.random() < 0.5
+    elif kind == "repro":
+        c["acc"] = "f64r"
+    elif kind == "snr":
+        c["call"], c["all_channels"] = "snr", True
+        c["n_snr"] = _log_int(rng, 16, 20_000)
+        c["r_k"], c["sub"] = rng.choice([2.0, 2.5, 3.0]), rng.choice([2, 4, 8])
+    elif kind == "create":
+        c["call"], c["max_new"], c["rho_tr"] = "create", 4096, 100.0
+        c["acc"], c["state"] = rng.choice([("f64", "f64"), ("fix64", "f64")])
+    # the tuning: what a context starts with, or one the tuner chooses for such shapes
+    if c["acc"] != "f64r" and rng.random() < 0.7:
+        c["tile_x"], c["tile_yz"], c["tile_block"] = rng.choice(
+            [(64, 4, 256), (128, 4, 256), (32, 4, 128), (16, 8, 256)])
+        c["fuse"] = rng.choice([2, 2, 2, 1])
+        c["count_lanes"] = rng.choice([1, 2, 4])
+    return c
+
+
+# ------------------------------------------------------------------ inputs
+
+def _edges(c):
+    """Per-axis box edges of a rectilinear level (log-uniform in [emin, emax])."""
+    if c["nb"] == 1:
+        return [[c["nx"]], [c["ny"]], [c["nz"]]]
+    rng = np.random.default_rng(c["layout"])
+    lo, hi = math.log(c["emin"]), math.log(c["emax"])
+    return [[int(v) for v in np.rint(np.exp(rng.uniform(lo, hi, c["nb"])))] for _ in range(3)]
+
+
+def _layout(c):
+    ex, ey, ez = _edges(c)
+    return W.rectilinear(ex, ey, ez)
+
+
+def _wrap(pos, domain):
+    d = torch.tensor(domain, dtype=torch.float64, device=DEV)
+    pos = torch.remainder(pos, d)
+    return torch.where(pos >= d, torch.zeros_like(pos), pos)
+
+
+def _uniform(g, n, domain):
+    u = torch.rand(n, 3, generator=g, dtype=torch.float64, device=DEV)
+    return _wrap(u * torch.tensor(domain, dtype=torch.float64, device=DEV), domain)
+
+
+def _plummer(g, n, a, centres, domain):
+    """Positions around `centres` [n, 3] from Plummer spheres of scale radius a."""
+    u = torch.rand(n, 3, generator=g, dtype=torch.float64, device=DEV)
+    r = a / torch.sqrt(torch.pow(u[:, 0].clamp(1e-9, 1 - 1e-9), -2.0 / 3.0) - 1.0)
+    mu, phi = 2.0 * u[:, 1] - 1.0, 2.0 * math.pi * u[:, 2]
+    s = torch.sqrt((1.0 - mu * mu).clamp_min(0.0))
+    d = torch.stack([s * torch.cos(phi), s * torch.sin(phi), mu], 1)
+    return _wrap(centres + r[:, None] * d, domain)
+
+
+def _positions(c, g, n, domain):
+    if c["spread"] == "uniform":
+        return _uniform(g, n, domain)
+    if c["spread"] == "plummer":
+        centre = torch.tensor([v / 2.0 for v in domain], dtype=torch.float64, device=DEV)
+        return _plummer(g, n, 8.0, centre[None, :], domain)
+    # half uniform, half in 32 clumps, in no order
+    nu = n // 2
+    centres = _uniform(g, 32, domain)
+    which = torch.randint(0, 32, (n - nu,), generator=g, device=DEV)
+    pos = torch.cat([_uniform(g, nu, domain), _plummer(g, n - nu, 8.0, centres[which], domain)])
+    return pos[torch.randperm(n, generator=g, device=DEV)]
+
+
+def _by_box(c, pos, cuts):
+    """The order that groups particles by box, and the boxes' offsets."""
+    nb = c["nb"]
+    n = pos.shape[0]
+    if nb == 1:
+        return None, torch.tensor([0, n], dtype=torch.int64, device=DEV)
+    ax = [torch.searchsorted(torch.as_tensor(np.asarray(cut), device=DEV),
+                             pos[:, a].floor().to(torch.int64).contiguous(), right=True) - 1
+          for a, cut in enumerate(cuts)]
+    box = (ax[2] * nb + ax[1]) * nb + ax[0]
+    order = torch.sort(box, stable=True)[1]
+    count = torch.bincount(box, minlength=nb ** 3)
+    off = torch.zeros(nb ** 3 + 1, dtype=torch.int64, device=DEV)
+    off[1:] = torch.cumsum(count, 0)
+    return order, off
+
+
+def _kind(c, g, n, domain, cuts, fields):
+    """One particle kind: contiguous float64 arrays x, y, z, then `fields` (values per
+    particle or one value for all), grouped by box, and the offsets."""
+    pos = _positions(c, g, n, domain)
+    order, off = _by_box(c, pos, cuts)
+    cols = {k: pos[:, a] for a, k in enumerate("xyz")}
+    for k, v in fields.items():
+        cols[k] = v if torch.is_tensor(v) else torch.full((n,), float(v), dtype=torch.float64,
+                                                          device=DEV)
+    if order is not None:
+        cols = {k: v[order] for k, v in cols.items()}
+    return {k: v.contiguous() for k, v in cols.items()}, off
+
+
+def _randn(g, n):
+    return torch.randn(n, generator=g, dtype=torch.float64, device=DEV)
+
+
+def _inputs(c, seed):
+    """The case's inputs, from the seed alone: layout, gas state (one [5, cells] draw in
+    the packed order of the library, box after box) and particles."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(int(seed))
+    domain, lo, n, cuts = _layout(c)
+    cells = [int(v) for v in np.prod(n.astype(np.int64), axis=1)]
+    total = sum(cells)
+    dt = STATE_DTYPE[c["state"]]
+    state = torch.empty(5 * total, dtype=dt, device=DEV)
+    off = 0
+    # log-normal density, Gaussian velocities, specific internal energy 1; drawn for whole
+    # domains of one box, and laid out box by box from one draw otherwise
+    rho = torch.exp((0.5 if c["n_snr"] else 1.0) * _randn(g, total))
+    if c["n_snr"]:
+        ix = torch.arange(total, device=DEV) % domain[0]
+        third = domain[0] // 3
+        rho *= torch.where(ix < third, 0.05, torch.where(ix < 2 * third, 1.0, 30.0)).double()
+    rho = rho.to(dt)
+    r64 = rho.double()
+    sv = 1.0 if c["n_snr"] else 0.3
+    parts = [rho]
+    p2 = torch.zeros(total, dtype=torch.float64, device=DEV)
+    for _ in range(3):
+        p = (r64 * _randn(g, total)).mul_(sv).to(dt)
+        p2 += p.double() ** 2
+        parts.append(p)
+    parts.append((r64 + 0.5 * p2 / r64).to(dt))
+    del p2, r64
+    if c["nb"] == 1:
+        for f in range(5):
+            state[f * total:(f + 1) * total] = parts[f]
+    else:
+        at = 0
+        stack = torch.stack(parts)
+        for nc in cells:
+            state[off:off + 5 * nc] = stack[:, at:at + nc].reshape(-1)
+            off += 5 * nc
+            at += nc
+        del stack
+    del parts
+    kinds = {}
+    if c["n_cic"]:
+        m = 0.1 + 0.9 * torch.rand(c["n_cic"], generator=g, dtype=torch.float64, device=DEV)
+        kinds["cic"] = _kind(c, g, c["n_cic"], domain, cuts, {"m": m})
+    if c["n_sn"]:
+        kinds["sn"] = _kind(c, g, c["n_sn"], domain, cuts, {"m": 1e-2, "e": 1.0, "r": c["r_sn"]})
+    if c["n_sink"]:
+        k = c["n_sink"]
+        f = {"a": 0.25}
+        if c["bondi"]:
+            u = torch.rand(k, generator=g, dtype=torch.float64, device=DEV)
+            f["m"] = torch.pow(10.0, 3.0 * u - 1.5)
+            f.update({v: 0.3 * _randn(g, k) for v in ("vx", "vy", "vz")})
+        kinds["sinks"] = _kind(c, g, k, domain, cuts, f)
+    if c["n_snr"]:
+        f = {"m": W.SNR_M_EJ, "e": W.SNR_E_SN}
+        f.update({v: 2.0 * _randn(g, c["n_snr"]) for v in ("vx", "vy", "vz")})
+        kinds["snr"] = _kind({**c, "spread": "uniform"}, g, c["n_snr"], domain, cuts, f)
+    return domain, lo, n, cuts, state, kinds
+
+
+# ------------------------------------------------------------- the program
+
+def _check(rc):
+    if rc != 0:
+        raise RuntimeError(B.lib.pmp_last_error().decode())
+
+
+class Program:
+    """What a program that uses the library keeps: a context and its arrays."""
+
+    def __init__(self, c, seed):
+        self.h = None
+        self.c = c
+        domain, lo, n, _cuts, self.state, kinds = _inputs(c, seed)
+        lo, n = (np.ascontiguousarray(v, dtype=np.int32) for v in (lo, n))
+        ch = 0
+        if not c["all_channels"]:
+            ch = B.PMP_CH_RHO if c["n_cic"] else 0
+            ch |= (B.PMP_CH_RHO | B.PMP_CH_E) if c["n_sn"] else 0
+            ch |= B.PMP_CH_K if c["n_sink"] else 0
+        st = B.PMP_STATE_F32 if c["state"] == "f32" else B.PMP_STATE_F64
+        layout = B.pmp_layout(lo.shape[0], lo.ctypes.data, n.ctypes.data, c["ghost"],
+                              (C.c_int32 * 3)(*domain), 1.0, B.ACC[c["acc"]], st,
+                              1 if c["n_sink"] else 0, ch, B.MARGIN_DEFAULT)
+        h = C.c_void_p()
+        _check(B.lib.pmp_create(C.byref(h), C.byref(layout)))
+        self.h = h
+        se, be, oc = C.c_int64(), C.c_int64(), C.c_int64()
+        _check(B.lib.pmp_sizes(h, C.byref(se), C.byref(be), C.byref(oc)))
+        assert se.value == self.state.numel()
+        self.buf = torch.zeros(be.value, dtype=ACC_DTYPE[c["acc"]], device=DEV)
+        self.lim = B.pmp_limits(1e-10, c["rho_tr"], 0.25, c["eint_mode"], 0.0, 1.0, 5.0 / 3.0)
+        self.keep = kinds
+        self.cic = self._struct(B.pmp_cic, "cic")
+        self.sn = self._struct(B.pmp_sn, "sn", r_max=float(c["r_sn"]))
+        self.sinks = self._struct(B.pmp_sinks, "sinks", r_k=float(c["r_k"]),
+                                  r_gauss=float(c["r_k"]) / 2.0, rate=1 if c["bondi"] else 0,
+                                  G=1.0, dt=0.05, gamma=5.0 / 3.0, lambda_=math.exp(1.5) / 4.0)
+        P = W.SnrParams()
+        self.snr = self._struct(B.pmp_snr, "snr", r_k=float(c["r_k"]), sub=c["sub"],
+                                nh_per_rho=P.nh_per_rho, msf_coef=P.msf_coef,
+                                psnr_coef=P.psnr_coef, eps_k=P.eps_k)
+        f64 = {"dtype": torch.float64, "device": DEV}
+        self.sink_out = torch.zeros(4, c["n_sink"], **f64) if c["n_sink"] else None
+        self.info = torch.zeros(4, c["n_snr"], **f64) if c["n_snr"] else None
+        if c["call"] == "create":
+            self.out = torch.zeros(7, c["max_new"], **f64)
+            self.work = torch.zeros(2 * c["max_new"] + 1, dtype=torch.int64, device=DEV)
+        if c["tile_x"]:
+            t = B.pmp_tuning()
+            _check(B.lib.pmp_get_tuning(h, C.byref(t)))
+            t.tile_x, t.tile_yz, t.tile_block = c["tile_x"], c["tile_yz"], c["tile_block"]
+            t.fuse_apply, t.count_lanes = c["fuse"], c["count_lanes"]
+            t.chunk_cic, t.chunk_sn = c["chunk_cic"], c["chunk_sn"]
+            _check(B.lib.pmp_set_tuning(h, C.byref(t)))
+        self.args = (_p(self.state), _p(self.buf), _r(self.cic), _r(self.sn), _r(self.sinks),
+                     C.byref(self.lim), _p(self.sink_out))
+        if c["call"] == "graph":
+            _check(B.lib.pmp_graph_build(h, 1, *self.args, _stream()))
+
+    def _struct(self, kind, name, **scalars):
+        if name not in self.keep:
+            return None
+        cols, off = self.keep[name]
+        s = kind()
+        for k, v in cols.items():
+            setattr(s, k, C.c_void_p(v.data_ptr()))
+        s.n, s.box_off = int(cols["x"].numel()), C.c_void_p(off.data_ptr())
+        for k, v in scalars.items():
+            setattr(s, k, v)
+        return s
+
+    def __del__(self):
+        if self.h is not None:
+            B.lib.pmp_destroy(self.h)
+            self.h = None
+
+
+def _p(t):
+    return None if t is None else C.c_void_p(t.data_ptr())
+
+
+def _r(s):
+    return None if s is None else C.byref(s)
+
+
+def _stream():
+    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+
+
+def prepare(case, seed):
+    return Program({**BASE, **case}, seed)
+
+
+def run(p):
+    call, lib, s = p.c["call"], B.lib, _stream()
+    out = {"state": p.state}
+    if p.sink_out is not None:
+        out["sinks"] = p.sink_out
+    if call == "graph":
+        _check(lib.pmp_graph_launch(p.h, s))
+    elif call in ("step", "create"):
+        _check(lib.pmp_step(p.h, *p.args, s))
+    else:
+        _check(lib.pmp_deposit(p.h, _p(p.buf), _p(p.state), _r(p.cic), _r(p.sn), _r(p.sinks),
+                               C.byref(p.lim), s))
+        if call == "snr":
+            _check(lib.pmp_deposit_snr(p.h, _p(p.buf), _p(p.state), _r(p.snr), _p(p.info), s))
+            out["info"] = p.info
+        _check(lib.pmp_ghost_fold(p.h, _p(p.buf), s))
+        if p.sinks is not None:
+            o = p.sink_out
+            _check(lib.pmp_sink_update(p.h, _p(p.state), _p(p.buf), _r(p.sinks), C.byref(p.lim),
+                                       _p(o[0]), _p(o[1]), _p(o[2]), _p(o[3]), s))
+        _check(lib.pmp_apply(p.h, _p(p.state), _p(p.buf), C.byref(p.lim), None, s))
+        out["buffer"] = p.buf
+    if call == "create":
+        owner = p.c["tile_x"] != 0 and p.c["fuse"] == 2  # such a step leaves no buffer behind
+        _check(lib.pmp_sink_create(p.h, _p(p.state), None if owner else _p(p.buf), _r(p.sinks),
+                                   float(p.c["r_k"]), C.byref(p.lim), p.c["max_new"], _p(p.out),
+                                   _p(p.work), s))
+        out["new"], out["count"] = p.out, p.work[:1]
+    return out
+
+
+# -------------------------------------------------------------------- work
+
+def work(case):
+    """Bytes of one pass: particle records in; of every cell that receives something five
+    state fields in, rho and E out (momentum too with remnants); a buffer that is a result
+    written once, or read and written once where the next call takes it.  Flops: the deposits'
+    and the limiter's."""
+    c = {**BASE, **case}
+    cells = float(np.prod([sum(e) for e in _edges(c)], dtype=np.float64))
+    s = 4 if c["state"] == "f32" else 8
+    b = 4 if c["acc"] == "f32" else 8
+    ball = 4.0 / 3.0 * math.pi
+    # cells reached: the share of the particles that is spread uniformly, and the clumps as a
+    # core of 40 cells across that every particle of theirs reaches
+    share = {"uniform": 1.0, "clumps": 0.5, "plummer": 0.0}[c["spread"]]
+    per = 8.0 * c["n_cic"] + ball * c["r_sn"] ** 3 * c["n_sn"]
+    core = (0 if share == 1.0 else 32 if c["spread"] == "clumps" else 1) * 40.0 ** 3
+    cov = 1.0 - math.exp(-(share * per + ball * 3.5 ** 3 * c["n_snr"]) / cells)
+    touched = min(cells, cov * cells + (1.0 - cov) * min(core, (1.0 - share) * per))
+    kern = ball * c["r_k"] ** 3 * c["n_sink"]
+    nbytes = 32.0 * c["n_cic"] + 48.0 * c["n_sn"] + 64.0 * c["n_snr"] + 32.0 * c["n_sink"]
+    nbytes += touched * (10 if c["n_snr"] else 7) * s + min(kern, cells) * 10 * s
+    if c["call"] in ("calls", "snr"):
+        fields = 5 if c["all_channels"] else 1 + (c["n_sn"] > 0)
+        pad = np.prod([sum(e) + 2 * c["ghost"] * len(e) for e in _edges(c)], dtype=np.float64)
+        nbytes += 2.0 * b * (fields + (c["n_sink"] > 0)) * pad
+    if c["call"] == "create":
+        nbytes += cells * s
+    flops = 60.0 * c["n_cic"] + 4.0 * ball * c["r_sn"] ** 3 * c["n_sn"] + 30.0 * touched
+    flops += 100.0 * kern + 8.0 * ball * 3.5 ** 3 * c["n_snr"] * c["sub"] ** 3
+    return {"bytes": float(nbytes), "flops": float(flops)}
+
+
+# ------------------------------------------------------- the same in 64 bits
+
+def _to_global(state, domain, lo, n):
+    """[5, nz, ny, nx] float64 of the packed state."""
+    X, Y, Z = domain
+    if len(lo) == 1:
+        return state.double().reshape(5, Z, Y, X).clone()
+    G = torch.empty(5, Z, Y, X, dtype=torch.float64, device=DEV)
+    at = 0
+    for (x, y, z), (a, b, d) in zip(lo.tolist(), n.tolist()):
+        m = a * b * d
+        G[:, z:z + d, y:y + b, x:x + a] = state[at:at + 5 * m].reshape(5, d, b, a).double()
+        at += 5 * m
+    return G
+
+
+def _to_packed(G, lo, n):
+    if len(lo) == 1:
+        return G.reshape(-1)
+    parts = []
+    for (x, y, z), (a, b, d) in zip(lo.tolist(), n.tolist()):
+        parts.append(G[:, z:z + d, y:y + b, x:x + a].reshape(-1))
+    return torch.cat(parts)
+
+
+class _Grid:
+    """The domain as one box with ghost zones, channels made when first added to."""
+
+    def __init__(self, domain, g):
+        self.d, self.g = domain, g
+        self.p = [v + 2 * g for v in domain]
+        self.ch = {}
+
+    def add(self, f, i, j, k, v):
+        if f not in self.ch:
+            self.ch[f] = torch.zeros(self.p[2] * self.p[1] * self.p[0], dtype=torch.float64,
+                                     device=DEV)
+        g = self.g
+        at = ((k + g) * self.p[1] + (j + g)) * self.p[0] + (i + g)
+        self.ch[f].index_add_(0, at, v)
+
+    def fold(self):
+        """Folded padded channels; the owned part is the sum over all periodic images."""
+        g, d = self.g, self.d
+        for f, A in self.ch.items():
+            A = A.reshape(self.p[2], self.p[1], self.p[0])
+            own = [slice(g, g + v) for v in (d[2], d[1], d[0])]
+            total = torch.zeros(d[2], d[1], d[0], dtype=torch.float64, device=DEV)
+            idx = [torch.arange(-g, v + g, device=DEV) % v for v in (d[2], d[1], d[0])]
+            t0 = torch.zeros(d[2], self.p[1], self.p[0], dtype=torch.float64, device=DEV)
+            t0.index_add_(0, idx[0], A)
+            t1 = torch.zeros(d[2], d[1], self.p[0], dtype=torch.float64, device=DEV)
+            t1.index_add_(1, idx[1], t0)
+            total.index_add_(2, idx[2], t1)
+            A[own[0], own[1], own[2]] = total
+            self.ch[f] = A
+            del t0, t1
+        return self
+
+    def owned(self, f):
+        g, d = self.g, self.d
+        if f not in self.ch:
+            return torch.zeros(d[2], d[1], d[0], dtype=torch.float64, device=DEV)
+        return self.ch[f][g:g + d[2], g:g + d[1], g:g + d[0]]
+
+
+def _cube(pos, r):
+    """Offsets around the host cells that hold every cell within r."""
+    q = int(math.floor(r)) + 1
+    host = pos.floor().to(torch.int64)
+    for dk in range(-q, q + 1):
+        for dj in range(-q, q + 1):
+            for di in range(-q, q + 1):
+                cell = host + torch.tensor([di, dj, dk], device=DEV)
+                yield cell, (cell.double() + 0.5) - pos
+
+
+def _in_ball(off, r):
+    return (off[:, 0] ** 2 + off[:, 1] ** 2) + off[:, 2] ** 2 <= r * r
+
+
+def _gather(G, cell, domain):
+    i, j, k = (torch.remainder(cell[:, a], domain[a]) for a in range(3))
+    return G[:, k, j, i]
+
+
+def _apply(G, Dr, q, DE, K, c):
+    """The limiter and the update (in place), and eta's removal Kl."""
+    rho, p, E = G[0], G[1:4], G[4]
+    tr = rho - c["rho_tr"]
+    Kl = torch.minimum(torch.maximum(torch.minimum(K, 0.25 * rho), tr), (rho - 1e-10).clamp_min(0))
+    Kl = torch.where(K > 0, Kl, torch.zeros_like(K))
+    f = 1.0 - Kl / rho
+    some = (Dr != 0) | (DE != 0) | (K != 0)
+    if q is not None:
+        some |= (q != 0).any(0)
+    p0 = f * p
+    rho1, E1 = f * rho + Dr, f * E + DE
+    emin = 0.0
+    if c["eint_mode"] == 1:
+        emin = rho1 * ((E - (p ** 2).sum(0) / (2.0 * rho)) / rho)
+    Kc = 2.0 * rho1 * (E1 - emin)
+    pp = (p0 ** 2).sum(0)
+    lam = torch.ones_like(rho)
+    if q is not None:
+        qq, pq = (q ** 2).sum(0), (p0 * q).sum(0)
+        g0 = pp - Kc
+        g1 = ((p0 + q) ** 2).sum(0) - Kc
+        root = torch.sqrt((pq * pq - qq * g0).clamp_min(0.0))
+        r = torch.where(pq > 0, -g0 / (pq + root), (root - pq) / qq).clamp(0.0, 1.0)
+        lam = torch.where(g1 > 0, torch.where(g0 <= 0, r, torch.zeros_like(r)), lam)
+    else:
+        g0 = pp - Kc
+    E1 = torch.where((g0 > 0) & (lam < 1) if q is not None else g0 > 0, emin + pp / (2.0 * rho1), E1)
+    G[0] = torch.where(some, rho1, rho)
+    G[1:4] = torch.where(some, p0 + (lam * q if q is not None else 0.0), p)
+    G[4] = torch.where(some, E1, E)
+    return Kl
+
+
+def exact(case, seed):
+    c = {**BASE, **case}
+    domain, lo, n, _cuts, state, kinds = _inputs(c, seed)
+    G = _to_global(state, domain, lo, n)
+    del state
+    D = _Grid(domain, c["ghost"])
+    if "cic" in kinds:
+        k = kinds["cic"][0]
+        t = torch.stack([k["x"], k["y"], k["z"]], 1) - 0.5
+        i0 = t.floor()
+        f = t - i0
+        i0 = i0.to(torch.int64)
+        for dk in (0, 1):
+            for dj in (0, 1):
+                for di in (0, 1):
+                    w = [f[:, a] if d else 1.0 - f[:, a] for a, d in enumerate((di, dj, dk))]
+                    D.add(0, i0[:, 0] + di, i0[:, 1] + dj, i0[:, 2] + dk,
+                          ((k["m"] * w[0]) * w[1]) * w[2])
+    if "sn" in kinds:
+        k = kinds["sn"][0]
+        pos = torch.stack([k["x"], k["y"], k["z"]], 1)
+        N = torch.zeros(pos.shape[0], dtype=torch.float64, device=DEV)
+        for _cell, off in _cube(pos, c["r_sn"]):
+            N += _in_ball(off, c["r_sn"])
+        for cell, off in _cube(pos, c["r_sn"]):
+            m = _in_ball(off, c["r_sn"]).nonzero().flatten()
+            if m.numel():
+                i, j, kk = (cell[m, a] for a in range(3))
+                D.add(0, i, j, kk, (k["m"] / N)[m])
+                D.add(4, i, j, kk, (k["e"] / N)[m])
+    out = {}
+    if "sinks" in kinds:
+        k = kinds["sinks"][0]
+        pos = torch.stack([k["x"], k["y"], k["z"]], 1)
+        r, ns = c["r_k"], pos.shape[0]
+        g2 = torch.full((ns,), (r / 2.0) ** 2, dtype=torch.float64, device=DEV)
+        req = None
+        if c["bondi"]:
+            S = torch.zeros(6, ns, dtype=torch.float64, device=DEV)
+            for cell, off in _cube(pos, r):
+                w = _in_ball(off, r).double()
+                u = _gather(G, cell, domain)
+                eint = (u[4] - (u[1:4] ** 2).sum(0) / (2.0 * u[0])).clamp_min(0.0)
+                cs = torch.sqrt(5.0 / 3.0 * (2.0 / 3.0) * eint / u[0])
+                S += w * torch.stack([torch.ones_like(w), u[0], u[1], u[2], u[3], u[0] * cs])
+            M = S[1]
+            v = S[2:5] / M - torch.stack([k["vx"], k["vy"], k["vz"]])
+            v2, c2 = (v ** 2).sum(0), (S[5] / M) ** 2
+            rbh = k["m"] / (v2 + c2)
+            lam = math.exp(1.5) / 4.0
+            mdot = 4.0 * math.pi * (M / S[0]) * rbh ** 2 * torch.sqrt(lam * lam * c2 + v2)
+            req = torch.minimum(0.05 * mdot, M)
+            g2 = rbh.clamp(0.25, r / 2.0) ** 2
+        Wt = torch.zeros(ns, dtype=torch.float64, device=DEV)
+        Mg = torch.zeros_like(Wt)
+        for cell, off in _cube(pos, r):
+            w = _in_ball(off, r).double()
+            Wt += w * torch.exp(-(off ** 2).sum(1) / g2)
+            Mg += w * _gather(G, cell, domain)[0]
+        if req is None:
+            req = k["a"] * Mg
+
+        def removal(off, u):
+            kr = req * torch.exp(-(off ** 2).sum(1) / g2) / Wt
+            return torch.maximum(kr, u[0] - c["rho_tr"])
+        for cell, off in _cube(pos, r):
+            m = _in_ball(off, r).nonzero().flatten()
+            if m.numel():
+                v = removal(off, _gather(G, cell, domain))[m]
+                D.add(5, cell[m, 0], cell[m, 1], cell[m, 2], v)
+    if "snr" in kinds:
+        out["info"] = _exact_snr(c, kinds["snr"][0], G, D, domain)
+    D.fold()
+    K = D.owned(5)
+    if "sinks" in kinds:
+        Kl = torch.minimum(torch.maximum(torch.minimum(K, 0.25 * G[0]), G[0] - c["rho_tr"]),
+                           (G[0] - 1e-10).clamp_min(0))
+        eta = torch.where(K > 0, Kl / K, torch.ones_like(K))[None]
+        so = torch.zeros(4, ns, dtype=torch.float64, device=DEV)
+        for cell, off in _cube(pos, r):
+            w = _in_ball(off, r).double()
+            u = _gather(G, cell, domain)
+            term = w * _gather(eta, cell, domain)[0] * removal(off, u)
+            so += torch.stack([term, *(term * u[a] / u[0] for a in (1, 2, 3))])
+        out["sinks"] = so
+    mom = torch.stack([D.owned(a) for a in (1, 2, 3)]) if c["n_snr"] else None
+    slabs = range(0, domain[2], 64)  # slab by slab: the temporaries of a large box are many
+    for z in slabs:
+        s = slice(z, z + 64)
+        _apply(G[:, s], D.owned(0)[s], None if mom is None else mom[:, s], D.owned(4)[s], K[s], c)
+    if c["call"] == "create":
+        out["new"], out["count"] = _exact_create(c, kinds, G, K, domain), None
+    out["state"] = _to_packed(G, lo, n)
+    if c["call"] in ("calls", "snr"):
+        have = [0, 1, 2, 3, 4] if c["all_channels"] else [0] + ([4] if c["n_sn"] else [])
+        have += [5] if c["n_sink"] else []
+        zero = torch.zeros(D.p[2], D.p[1], D.p[0], dtype=torch.float64, device=DEV)
+        out["buffer"] = None
+        if c["acc"] != "fix64":
+            out["buffer"] = torch.cat([D.ch.get(f, zero).reshape(-1) for f in have])
+    return out
+
+
+def _exact_snr(c, k, G, D, domain):
+    """Remnants with the TIGRESS variant, added to D; returns V_snr, M_snr, n_H, |p_rad|."""
+    P = W.SnrParams()
+    pos = torch.stack([k["x"], k["y"], k["z"]], 1)
+    vs = torch.stack([k["vx"], k["vy"], k["vz"]])
+    r, ns = c["r_k"], c["sub"]
+    sub = (torch.arange(ns, dtype=torch.float64, device=DEV) + 0.5) / ns
+
+    def covered(cell):
+        d = [(cell[:, a, None].double() + sub[None]) - pos[:, a, None] for a in range(3)]
+        near = [v.abs().min(1)[0] for v in d]
+        m = ((near[0] ** 2 + near[1] ** 2) + near[2] ** 2 <= r * r * (1 + 1e-9)).nonzero().flatten()
+        w = torch.zeros(pos.shape[0], dtype=torch.float64, device=DEV)
+        if m.numel():
+            x2, y2, z2 = (v[m] ** 2 for v in d)
+            t = (x2[:, None, None, :] + y2[:, None, :, None]) + z2[:, :, None, None]
+            w[m] = (t <= r * r).double().sum((1, 2, 3)) / ns ** 3
+        return w
+    S = torch.zeros(5, pos.shape[0], dtype=torch.float64, device=DEV)
+    for cell, _off in _cube(pos, r + 1.0):
+        w = covered(cell)
+        S += w * torch.cat([torch.ones_like(w)[None], _gather(G, cell, domain)[:4]])
+    V, Msnr = S[0], S[1] + k["m"]
+    nH = Msnr / V * P.nh_per_rho
+    RM = Msnr / (P.msf_coef * nH ** -0.26)
+    p = torch.where(RM > 1.0, P.psnr_coef * nH ** -0.17,
+                    torch.where(RM > 0.027, torch.sqrt(2.0 * k["m"] * P.eps_k * k["e"]),
+                                torch.zeros_like(RM)))
+    vc = (S[2:5] + k["m"] * vs) / Msnr
+    Eall = k["e"] + 0.5 * k["m"] * (vs ** 2).sum(0)
+    for cell, off in _cube(pos, r + 1.0):
+        w = covered(cell)
+        m = (w > 0).nonzero().flatten()
+        if not m.numel():
+            continue
+        u = _gather(G, cell[m], domain)
+        wm, o, a = w[m], off[m], w[m] / V[m]
+        ln = (o ** 2).sum(1).sqrt()
+        rad = torch.where(ln > 0, a * p[m] / ln, torch.zeros_like(ln)) * o.T
+        i, j, kk = (cell[m, q] for q in range(3))
+        D.add(0, i, j, kk, a * k["m"][m])
+        D.add(4, i, j, kk, a * Eall[m] + (vc[:, m] * rad).sum(0))
+        for q in range(3):
+            D.add(1 + q, i, j, kk,
+                  wm * ((u[0] + k["m"][m] / V[m]) * vc[q, m] - u[1 + q]) + rad[q])
+    return torch.stack([V, Msnr, nH, p])
+
+
+def _exact_create(c, kinds, G, K, domain):
+    """New sinks of the updated state G (changed in place): [7, max_new]."""
+    r, rtr = c["r_k"], c["rho_tr"]
+    rho = G[0]
+    X, Y, Z = domain
+    buf_given = not (c["tile_x"] and c["fuse"] == 2)
+    cand = rho > rtr
+    if buf_given:
+        cand &= K == 0
+    at = cand.nonzero()
+    q = int(math.floor(r))
+    ok = torch.ones(at.shape[0], dtype=torch.bool, device=DEV)
+    mine = rho[at[:, 0], at[:, 1], at[:, 2]]
+    for dk in range(-q, q + 1):
+        for dj in range(-q, q + 1):
+            for di in range(-q, q + 1):
+                if di * di + dj * dj + dk * dk > r * r or (di, dj, dk) == (0, 0, 0):
+                    continue
+                o = rho[torch.remainder(at[:, 0] + dk, Z), torch.remainder(at[:, 1] + dj, Y),
+                        torch.remainder(at[:, 2] + di, X)]
+                ok &= ~(o > mine)
+    s = kinds["sinks"][0]
+    for a in range(s["x"].shape[0]):
+        d2 = torch.zeros_like(mine)
+        for axis, name, dom in ((2, "x", X), (1, "y", Y), (0, "z", Z)):
+            d = (at[:, axis].double() + 0.5 - s[name][a]).abs()
+            d2 += torch.minimum(d, dom - d) ** 2
+        ok &= d2 > r * r
+    at = at[ok]
+    new = torch.zeros(7, c["max_new"], dtype=torch.float64, device=DEV)
+    if at.shape[0] > c["max_new"]:
+        return new
+    u = G[:, at[:, 0], at[:, 1], at[:, 2]]
+    m = u[0] - rtr
+    k = at.shape[0]
+    new[0, :k], new[1, :k], new[2, :k] = (at[:, a].double() + 0.5 for a in (2, 1, 0))
+    new[3, :k] = m
+    new[4:7, :k] = m * u[1:4] / u[0]
+    G[:, at[:, 0], at[:, 1], at[:, 2]] = u / u[0] * rtr
+    return new
