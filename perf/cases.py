@@ -38,7 +38,7 @@ BASE = {
     "call": "step", "nx": 64, "ny": 64, "nz": 64,
     "nb": 1, "emin": 8, "emax": 64, "layout": 5,   # nb > 1: nb^3 boxes, edges drawn from `layout`
     "ghost": 4, "acc": "f64", "state": "f64", "all_channels": False, "eint_mode": 0,
-    "n_cic": 0, "n_sn": 0, "r_sn": 3.0, "spread": "uniform",
+    "n_cic": 0, "m_scale": 1.0, "n_sn": 0, "r_sn": 3.0, "spread": "uniform",
     "n_sink": 0, "bondi": False, "r_k": 4.0, "rho_tr": math.inf,
     "n_snr": 0, "sub": 4, "max_new": 0,
     "tile_x": 0, "tile_yz": 4, "tile_block": 256, "fuse": 2, "chunk_cic": 16384,
@@ -88,9 +88,11 @@ def listed():
         # resolved supernova remnants with the TIGRESS variant over gas of three densities
         _case("snr_256_f64", call="snr", nx=256, ny=256, nz=256, n_cic=100_000, n_snr=20_000,
               r_k=3.0, all_channels=True),
-        # a star-forming core: the step, then the search for new sinks
+        # a star-forming core: the step, then the search for new sinks; the particles carry little
+        # mass, so that passes over one state, as successive steps of a run, find few
         _case("create_256_f64", call="create", nx=256, ny=256, nz=256, n_cic=1_000_000,
-              spread="plummer", n_sink=256, rho_tr=100.0, max_new=4096, tile_x=16, tile_yz=8),
+              m_scale=1e-3, spread="plummer", n_sink=256, rho_tr=100.0, max_new=4096, tile_x=16,
+              tile_yz=8),
     ]
 
 
@@ -140,7 +142,7 @@ def draw(rng):
         c["n_snr"] = _log_int(rng, 16, 20_000)
         c["r_k"], c["sub"] = rng.choice([2.0, 2.5, 3.0]), rng.choice([2, 4, 8])
     elif kind == "create":
-        c["call"], c["max_new"], c["rho_tr"] = "create", 4096, 100.0
+        c["call"], c["max_new"], c["rho_tr"], c["m_scale"] = "create", 4096, 100.0, 1e-3
         c["acc"], c["state"] = rng.choice([("f64", "f64"), ("fix64", "f64")])
     # the tuning: what a context starts with, or one the tuner chooses for such shapes
     if c["acc"] != "f64r" and rng.random() < 0.7:
@@ -281,7 +283,8 @@ def _inputs(c, seed):
     kinds = {}
     if c["n_cic"]:
         m = 0.1 + 0.9 * torch.rand(c["n_cic"], generator=g, dtype=torch.float64, device=DEV)
-        kinds["cic"] = _kind(c, g, c["n_cic"], domain, cuts, {"m": m})
+        kinds["cic"] = _kind(c, g, c["n_cic"], domain, cuts,
+                             {"m": c["m_scale"] * m})
     if c["n_sn"]:
         kinds["sn"] = _kind(c, g, c["n_sn"], domain, cuts, {"m": 1e-2, "e": 1.0, "r": c["r_sn"]})
     if c["n_sink"]:
