@@ -312,6 +312,8 @@ struct SnrArgs {
   const long long* box_off;
   double r_k, nh_per_rho, msf_coef, psnr_coef, eps_k;
   int sub;
+  int side;      // cells per axis of the LDS tables (set by the launcher)
+  int list_cap;  // covered cells a remnant's list holds, 0: no list (set by the launcher)
 };
 hipError_t launch_snr_deposit(const Mesh& M, const SnrArgs& A, const void* state, void* buf,
                               double* info, hipStream_t s);

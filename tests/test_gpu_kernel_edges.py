@@ -1,0 +1,34 @@
+"""Edges of the kernels' tilings and of the dispatch rules between them, on the
+GPU against the serial oracle: fixed point bit for bit, FP64 within 1e-12 of
+each field's largest magnitude (the accumulation's rounding, as in the other
+parity tests)."""
+import dataclasses
+
+import numpy as np
+import pytest
+
+from paper_2509_18261_amd import workloads as W
+
+from test_gpu_snr import B, check  # noqa: F401  (B is the binding fixture)
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("acc", ["fix64", "f64"])
+@pytest.mark.parametrize("r_k,sub", [(0.0, 16), (0.5, 2), (1.0, 1), (2.5, 8), (5.0, 2), (9.25, 1),
+                                     (16.0, 16)])
+def test_snr_kernel_sizes(B, orc, r_k, sub, acc):  # noqa: F811
+    """Remnant kernels from the host cell alone to the largest radius and
+    finest sampling (the longest cell list in LDS), with remnants on cell
+    corners, centres and sample points (exact ties of the distance test) and
+    at domain corners (kernels that wrap)."""
+    w = W.snr_box(nx=36, n_snr=3, seed=31, dtype=np.float64)
+    pts = np.array([[18.0, 18.0, 18.0], [7.5, 20.5, 30.5], [0.0, 35.999, 0.25],
+                    [12.0 + 0.5 / sub, 9.0 + 0.5 / sub, 17.0 + 0.5 / sub], [3.3, 30.1, 11.7]])
+    n = len(pts)
+    f = {"m": np.full(n, W.SNR_M_EJ), "e": np.full(n, W.SNR_E_SN)}
+    vel = np.random.default_rng(5).standard_normal((3, n))
+    f.update(vx=vel[0], vy=vel[1], vz=vel[2])
+    w = dataclasses.replace(w, name=f"snr_r{r_k}_s{sub}", ghost=17, snr=W._one_box(pts, f),
+                            snr_params=dataclasses.replace(w.snr_params, r_k=r_k, sub=sub))
+    check(B, orc, w, acc)
