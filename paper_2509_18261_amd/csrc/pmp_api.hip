@@ -258,11 +258,10 @@ void free_bin_work(pmp_ctx* c) {
   (void)hipFree(w.hist);
   (void)hipFree(w.block_sums);
   (void)hipFree(w.cic_tmp);
-  (void)hipFree(w.cic_tmp_tile);
+  (void)hipFree(w.cic_idx);
   (void)hipFree(w.cic_rec);
   (void)hipFree(w.cic_off);
   (void)hipFree(w.sn_tmp);
-  (void)hipFree(w.sn_tmp_tile);
   (void)hipFree(w.sn_rec);
   (void)hipFree(w.sn_off);
   (void)hipFree(w.sn_pk);
@@ -694,7 +693,7 @@ template <class T> int regrow(T** p, long long have, long long need) {
 struct BinSizes {
   int shift = 0, nb = 0;
   long long hist = 0, blocks = 0, tiles1 = 0, partial = 0, slot_cap = 0, cic_cap = 0,
-            sn_cap = 0, hist2 = 0, blocks2 = 0, slice_base = 0, n_sn = 0;
+            sn_cap = 0, hist2 = 0, blocks2 = 0, slice_base = 0, n_sn = 0, n_cic = 0;
 };
 
 // The step runs on owner tiles (no ghost zone, no fold): tuning fuse_apply 2
@@ -730,24 +729,18 @@ int bin_sizes(const pmp_ctx* c, long long n_cic, long long n_sn, double r_max, B
   const long long cic_cap = std::max<long long>(8 * n_cic, 1);
   const long long sn_cap = std::max<long long>(maxt * n_sn, 1);
   const long long full_slices = (cic_cap + kSlice - 1) / kSlice + (sn_cap + kSlice - 1) / kSlice;
-  // coarse buckets of 2^shift consecutive tiles (at most 1024 buckets, at
-  // most 8192 tiles per bucket; sized for the padded grid, which never has
-  // fewer tiles than the owner grid): the shift that minimises the histogram work,
-  // level 1 (nb x blocks counts, written one cache line apart, weighted 4)
-  // plus level 2 (2^shift x slices counts, zeroed and scanned)
-  int shift = -1;
-  double best = 0.0;
-  for (int sh = 0; sh <= 13; ++sh) {
-    const long long nbs_ = (c->ntiles + (1ll << sh) - 1) >> sh;
-    if (nbs_ > 1024) continue;
-    const double cost = 4.0 * (double)nbs_ * (double)(nbc + nbs) +
-                        (double)(1ll << sh) * (double)(full_slices + 2 * nbs_);
-    if (shift < 0 || cost < best) {
-      shift = sh;
-      best = cost;
-    }
-  }
-  if (shift < 0) return fail(PMP_ERANGE, "binned deposit: too many tiles (%lld)", c->ntiles);
+  // coarse buckets of 2^shift consecutive tiles: at most 512 buckets, or 1024
+  // where that would put more than 256 tiles in one (sized for the padded
+  // grid, which never has fewer tiles than the owner grid).  Fewer buckets
+  // give longer runs in level 1, fewer tiles per bucket in level 2: at 512^3
+  // the binning takes 220 us with 264 buckets of 256 tiles and 230 us with
+  // 528 of 128; on the 4096-box level 690 us with 1024 buckets and 770 us
+  // with 512.  The shift depends on the tiles alone, so that the scratch for
+  // fewer particles is never larger.
+  int shift = 0;
+  while (shift <= 13 && ((c->ntiles + (1ll << shift) - 1) >> shift) > (shift < 8 ? 512 : 1024))
+    ++shift;
+  if (shift > 13) return fail(PMP_ERANGE, "binned deposit: too many tiles (%lld)", c->ntiles);
   z.shift = shift;
   z.nb = (int)((c->ntiles + (1ll << shift) - 1) >> shift);
   z.hist = (long long)z.nb * (nbc + nbs) + 1;
@@ -764,6 +757,7 @@ int bin_sizes(const pmp_ctx* c, long long n_cic, long long n_sn, double r_max, B
   z.sn_cap = sn_cap;
   z.slice_base = 2 * (long long)z.nb + 1;
   z.n_sn = std::max<long long>(n_sn, 1);
+  z.n_cic = std::max<long long>(n_cic, 1);
   if (cic_cap >= (1ll << 31) || sn_cap >= (1ll << 31) || z.hist >= (1ll << 31) ||
       z.hist2 >= (1ll << 31))
     return fail(PMP_ERANGE, "binned deposit: too many tile entries");
@@ -794,11 +788,10 @@ size_t carve_bin(const BinSizes& z, char* base, BinWork* w) {
   take(W.heavy_unit, z.slot_cap);
   take(W.arrive, z.slot_cap);
   take(W.heavy_count, 1);
+  take(W.cic_rec, z.n_cic);
   take(W.cic_tmp, z.cic_cap);
-  take(W.cic_tmp_tile, z.cic_cap);
-  take(W.cic_rec, z.cic_cap);
+  take(W.cic_idx, z.cic_cap);
   take(W.sn_tmp, z.sn_cap);
-  take(W.sn_tmp_tile, z.sn_cap);
   take(W.sn_rec, z.sn_cap);
   take(W.hist2, z.hist2);
   take(W.block_sums2, z.blocks2);
@@ -877,13 +870,12 @@ int ensure_bin_work(pmp_ctx* c, long long n_cic, long long n_sn, double r_max, h
   }
   if (!rc && cic_cap > w.cic_cap) {
     rc = regrow(&w.cic_tmp, 0, cic_cap);
-    if (!rc) rc = regrow(&w.cic_tmp_tile, 0, cic_cap);
-    if (!rc) rc = regrow(&w.cic_rec, 0, cic_cap);
+    if (!rc) rc = regrow(&w.cic_idx, 0, cic_cap);
+    if (!rc) rc = regrow(&w.cic_rec, 0, cic_cap / 8 + 1);  // cic_cap = 8 n_cic
     if (!rc) w.cic_cap = cic_cap;
   }
   if (!rc && sn_cap > w.sn_cap) {
     rc = regrow(&w.sn_tmp, 0, sn_cap);
-    if (!rc) rc = regrow(&w.sn_tmp_tile, 0, sn_cap);
     if (!rc) rc = regrow(&w.sn_rec, 0, sn_cap);
     if (!rc) w.sn_cap = sn_cap;
   }

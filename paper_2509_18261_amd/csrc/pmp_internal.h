@@ -198,12 +198,11 @@ struct BinWork {
   int nblk_cic, nblk_sn;  // level-1 blocks per kind
   int* hist;            // [nbuckets * (nblk_cic + nblk_sn) + 1]: histograms, then scanned
   int* block_sums;      // scan scratch
-  double4* cic_tmp;     // level-1 output, grouped by bucket
-  int* cic_tmp_tile;
-  double4* cic_rec;     // level-2 output, grouped by tile
+  double4* cic_rec;     // [n_cic] (x, y, z, m) of each particle
+  int2* cic_tmp;        // level-1 output: (particle, tile), grouped by bucket
+  int* cic_idx;         // level-2 output: particle indices grouped by tile
   int* cic_off;         // [ntiles + 1]
-  int* sn_tmp;           // supernova entries: particle indices
-  int* sn_tmp_tile;
+  int2* sn_tmp;          // supernova entries: (particle, tile)
   int* sn_rec;           // sorted by tile: particle index
   int* sn_off;          // [ntiles + 1]
   SnPk* sn_pk;          // [n_sn]

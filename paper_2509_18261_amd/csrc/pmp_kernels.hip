@@ -130,6 +130,23 @@ __device__ __forceinline__ int find_box_in(const long long* off, int lo, int hi,
   return lo;
 }
 
+// find_box by a whole wavefront: each step loads 64 evenly spaced offsets at
+// once, so 4096 boxes take two dependent loads where a binary search takes
+// twelve.  Call from every lane of the wavefront with the same p.
+__device__ __forceinline__ int find_box_wave(const long long* off, int nbox, long long p) {
+  const int lane = threadIdx.x & (kWave - 1);
+  int lo = 0, n = nbox;
+  while (n > 1) {
+    const int step = (n + kWave - 1) / kWave;
+    const int i = lane * step;
+    const int c = __popcll(__ballot(i < n && off[lo + i] <= p));  // lane 0 always counts
+    const int k = (c > 0 ? c - 1 : 0) * step;
+    lo += k;
+    n = min(step, n - k);
+  }
+  return lo;
+}
+
 // Boxes holding particles [p0, p1) of a block (shared by the block): two
 // searches per block, after which each particle's search is over the few
 // boxes in between.  Call from every thread of the block.
@@ -140,9 +157,11 @@ __device__ __forceinline__ void block_box_range(const long long* off, int nbox, 
     b0 = b1 = 0;
     return;
   }
-  if (threadIdx.x == 0) sb[0] = find_box(off, nbox, p0);
-  if (threadIdx.x == 1 || (blockDim.x == 1 && threadIdx.x == 0))
-    sb[1] = find_box(off, nbox, max(p0, p1 - 1));
+  const int w = threadIdx.x / kWave;  // blocks of at least two wavefronts
+  if (w < 2) {
+    const int b = find_box_wave(off, nbox, w ? max(p0, p1 - 1) : p0);
+    if ((threadIdx.x & (kWave - 1)) == 0) sb[w] = b;
+  }
   __syncthreads();
   b0 = sb[0];
   b1 = sb[1];
@@ -2220,9 +2239,10 @@ __global__ __launch_bounds__(kScanBlock) void k_scan_finish(int* __restrict__ of
 // Level 1 of the bucket sort, CIC.  Block k handles particles
 // [k * kBinChunkCic, (k + 1) * kBinChunkCic).  Histogram pass (SCATTER =
 // false): LDS counts of (particle, tile) pairs per coarse bucket, written to
-// hist[bucket * nblk + k].  Scatter pass: hist holds the scanned positions;
-// LDS cursors hand out slots and each pair's record (x, y, z, m) and tile are
-// written there, so a block writes runs of consecutive slots per bucket.
+// hist[bucket * nblk + k], and each particle's (x, y, z, m) written as one
+// record.  Scatter pass: hist holds the scanned positions; LDS cursors hand
+// out slots and each (particle, tile) pair is written there, so a block
+// writes runs of consecutive slots per bucket.
 // Column of level-1 block blk in a bucket's row of the histogram: blocks
 // grouped by XCD (block i runs on XCD i mod 8), so that the counts sharing a
 // cache line come from one XCD and merge in its L2.  A bijection on
@@ -2249,7 +2269,7 @@ template <bool SCATTER, int OWN>
 __device__ __forceinline__ void l1_cic(int blk, const Mesh& M, const TileGrid& T,
                                        const Particles& P, int shift, int nb,
                                        int* __restrict__ hist, int nblk,
-                                       double4* __restrict__ tmp, int* __restrict__ tmp_tile,
+                                       double4* __restrict__ aos, int2* __restrict__ tmp,
                                        long long cap, NbrBox* s_nbr) {
   extern __shared__ int h[];
   const int g = M.ghost;
@@ -2272,10 +2292,25 @@ __device__ __forceinline__ void l1_cic(int blk, const Mesh& M, const TileGrid& T
   for (int u = 0; u < UNR; ++u) {
     const long long p = p0 + threadIdx.x + (long long)u * blockDim.x;
     if (p < p1) {
-      px[u] = P.x[p];
-      py[u] = P.y[p];
-      pz[u] = P.z[p];
-      pm[u] = P.a[p];
+      if constexpr (SCATTER) {
+        const double4 v = aos[p];
+        px[u] = v.x;
+        py[u] = v.y;
+        pz[u] = v.z;
+        pm[u] = v.w;
+      } else {
+        px[u] = P.x[p];
+        py[u] = P.y[p];
+        pz[u] = P.z[p];
+        pm[u] = P.a[p];
+      }
+    }
+  }
+  if constexpr (!SCATTER) {
+#pragma unroll
+    for (int u = 0; u < UNR; ++u) {
+      const long long p = p0 + threadIdx.x + (long long)u * blockDim.x;
+      if (p < p1) aos[p] = make_double4(px[u], py[u], pz[u], pm[u]);
     }
   }
   unsigned slow = 0;  // owner tiles: particles whose stencil leaves their box
@@ -2316,8 +2351,7 @@ __device__ __forceinline__ void l1_cic(int blk, const Mesh& M, const TileGrid& T
           const int pos = atomicAdd(h + (t >> shift), 1);
           if (SCATTER) {
             if (pos < cap) {
-              tmp[pos] = make_double4(x, y, z, m);
-              tmp_tile[pos] = t;
+              tmp[pos] = make_int2((int)p, t);
             } else {
               full = true;
             }
@@ -2350,15 +2384,14 @@ __device__ __forceinline__ void l1_cic(int blk, const Mesh& M, const TileGrid& T
       const long long p = p0 + (sv & (kBinChunkCic - 1));
       const int b = packed ? bb0 + (sv >> kChunkBits) : find_box_in(P.box_off, bb0, bb1, p);
       const DevBox B = M.boxes[b];
-      const double x = P.x[p], y = P.y[p], z = P.z[p], m = P.a[p];
+      const double x = P.x[p], y = P.y[p], z = P.z[p];
       int lo[3], hi[3];
       cic_box(B, g, x, y, z, lo, hi);
       particle_tiles<OWN>(M, T, b, B, lo, hi, [&](int t) {
         const int pos = atomicAdd(h + (t >> shift), 1);
         if (SCATTER) {
           if (pos < cap) {
-            tmp[pos] = make_double4(x, y, z, m);
-            tmp_tile[pos] = t;
+            tmp[pos] = make_int2((int)p, t);
           } else {
             full = true;
           }
@@ -2560,9 +2593,8 @@ template <int OWN>
 __device__ __forceinline__ void l1_sn_scatter(int blk, const Mesh& M, const TileGrid& T,
                                               const Particles& P, int shift, int nb,
                                               int* __restrict__ hist, int nblk,
-                                              const SnPk* __restrict__ pk, int* __restrict__ tmp,
-                                              int* __restrict__ tmp_tile, long long cap,
-                                              NbrBox* s_nbr) {
+                                              const SnPk* __restrict__ pk, int2* __restrict__ tmp,
+                                              long long cap, NbrBox* s_nbr) {
   extern __shared__ int h[];
   const int col = hist_col(blk, nblk);
   for (int c = threadIdx.x; c < nb; c += blockDim.x)
@@ -2583,8 +2615,7 @@ __device__ __forceinline__ void l1_sn_scatter(int blk, const Mesh& M, const Tile
     sn_tiles<OWN>(M, T, b, B, R.x, R.y, R.z, R.r, N, [&](int id) {
       const int pos = atomicAdd(h + (id >> shift), 1);
       if (pos < cap) {
-        tmp[pos] = (int)p;
-        tmp_tile[pos] = id;
+        tmp[pos] = make_int2((int)p, id);
       } else {
         full = true;
       }
@@ -2601,10 +2632,11 @@ template <int OWN>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(7))) void k_l1_hist(Mesh M, TileGrid T, Particles C, Particles Sn,
                                                 int shift, int nb, int* __restrict__ hc, int nbc,
                                                 int* __restrict__ hs, int nbs,
-                                                const SnPk* __restrict__ pk) {
+                                                const SnPk* __restrict__ pk,
+                                                double4* __restrict__ aos) {
   __shared__ NbrBox s_nbr[OWN == 1 ? 27 * kNbrCache : 1];
   if ((int)blockIdx.x < nbc)
-    l1_cic<false, OWN>(blockIdx.x, M, T, C, shift, nb, hc, nbc, nullptr, nullptr, 0, s_nbr);
+    l1_cic<false, OWN>(blockIdx.x, M, T, C, shift, nb, hc, nbc, aos, nullptr, 0, s_nbr);
   else
     l1_sn_hist<OWN>(blockIdx.x - nbc, M, T, Sn, shift, nb, hs, nbs, pk, s_nbr);
 }
@@ -2614,17 +2646,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) void k
                                                    Particles Sn, int shift, int nb,
                                                    int* __restrict__ hc, int nbc,
                                                    int* __restrict__ hs, int nbs,
-                                                   double4* __restrict__ ctmp,
-                                                   int* __restrict__ ctmp_tile, long long ccap,
+                                                   double4* __restrict__ aos,
+                                                   int2* __restrict__ ctmp, long long ccap,
                                                    const SnPk* __restrict__ pk,
-                                                   int* __restrict__ stmp,
-                                                   int* __restrict__ stmp_tile, long long scap) {
+                                                   int2* __restrict__ stmp, long long scap) {
   __shared__ NbrBox s_nbr[OWN == 1 ? 27 * kNbrCache : 1];
   if ((int)blockIdx.x < nbc)
-    l1_cic<true, OWN>(blockIdx.x, M, T, C, shift, nb, hc, nbc, ctmp, ctmp_tile, ccap, s_nbr);
+    l1_cic<true, OWN>(blockIdx.x, M, T, C, shift, nb, hc, nbc, aos, ctmp, ccap, s_nbr);
   else
-    l1_sn_scatter<OWN>(blockIdx.x - nbc, M, T, Sn, shift, nb, hs, nbs, pk, stmp, stmp_tile, scap,
-                       s_nbr);
+    l1_sn_scatter<OWN>(blockIdx.x - nbc, M, T, Sn, shift, nb, hs, nbs, pk, stmp, scap, s_nbr);
 }
 
 // Level 2: one workgroup per coarse bucket sorts the bucket's records by
@@ -2656,8 +2686,11 @@ __device__ __forceinline__ void bucket_range(const L2Geom& G, int cc, long long&
   end = min((long long)H[(long long)(c + 1) * nblk] - base, cap);
 }
 
-// One block: slices per bucket, their exclusive prefix (slice_base), and the
-// tile offsets of empty buckets and the kinds' totals.
+// One block: slices per bucket and their exclusive prefix (slice_base).  An
+// empty bucket of a kind that has particles keeps one empty slice, which
+// writes its tiles' offsets in the passes below (one thread of this block
+// writing them took up to 125 us for a kind without particles); also the
+// kinds' totals.
 __global__ __launch_bounds__(1024) void k_l2_plan(L2Geom G, int* __restrict__ slice_base,
                                                   int* __restrict__ off0,
                                                   int* __restrict__ off1,
@@ -2674,17 +2707,13 @@ __global__ __launch_bounds__(1024) void k_l2_plan(L2Geom G, int* __restrict__ sl
     const int cc = base_c + threadIdx.x;
     int ns = 0;
     if (cc < n) {
-      long long start, end;
-      bucket_range(G, cc, start, end);
-      ns = (int)((end - start + kSlice - 1) / kSlice);
       const int kind = cc >= G.nb, c = cc - kind * G.nb;
-      int* off = kind ? off1 : off0;
-      if (ns == 0) {
-        const long long t0 = (long long)c << G.shift;
-        const int nf = (int)min((long long)1 << G.shift, G.ntiles - t0);
-        for (int f = 0; f < nf; ++f) off[t0 + f] = (int)start;
+      if ((kind ? G.nblk1 : G.nblk0) > 0) {
+        long long start, end;
+        bucket_range(G, cc, start, end);
+        ns = max(1, (int)((end - start + kSlice - 1) / kSlice));
+        if (c == G.nb - 1) (kind ? off1 : off0)[G.ntiles] = (int)end;
       }
-      if (c == G.nb - 1) off[G.ntiles] = (int)end;
     }
     const int inc = block_inclusive_scan(ns, sh);
     const int cv = carry;
@@ -2709,8 +2738,8 @@ __device__ __forceinline__ int find_slice(const int* slice_base, int n, int q) {
 // written to hist2[2^shift * slice_base[cc] + f * ns + q] (bucket, tile,
 // slice order), so that one exclusive scan of hist2 gives final positions.
 __global__ __launch_bounds__(256) void k_l2_hist(L2Geom G, const int* __restrict__ slice_base,
-                                                const int* __restrict__ tile0,
-                                                const int* __restrict__ tile1, long long cap0,
+                                                const int2* __restrict__ tmp0,
+                                                const int2* __restrict__ tmp1, long long cap0,
                                                 long long cap1, int* __restrict__ hist2) {
   extern __shared__ int h[];
   const int nf_max = 1 << G.shift;
@@ -2724,11 +2753,11 @@ __global__ __launch_bounds__(256) void k_l2_hist(L2Geom G, const int* __restrict
     // records past the capacity were never written (flagged by level 1)
     const long long e0 = start + (long long)q * kSlice;
     const long long e1 = min(min(e0 + kSlice, end), kind ? cap1 : cap0);
-    const int* tt = kind ? tile1 : tile0;
+    const int2* tt = kind ? tmp1 : tmp0;
     const int t0 = c << G.shift;
     for (int f = threadIdx.x; f < nf_max; f += blockDim.x) h[f] = 0;
     __syncthreads();
-    for (long long e = e0 + threadIdx.x; e < e1; e += blockDim.x) atomicAdd(h + (tt[e] - t0), 1);
+    for (long long e = e0 + threadIdx.x; e < e1; e += blockDim.x) atomicAdd(h + (tt[e].y - t0), 1);
     __syncthreads();
     const long long o = (long long)nf_max * slice_base[cc];
     for (int f = threadIdx.x; f < nf_max; f += blockDim.x) hist2[o + (long long)f * ns + q] = h[f];
@@ -2736,97 +2765,59 @@ __global__ __launch_bounds__(256) void k_l2_hist(L2Geom G, const int* __restrict
   }
 }
 
-// Per slice of one kind: LDS cursors from the scanned hist2 place every
-// record at its final position, grouped by tile; slice 0 of a bucket writes
-// the offsets of the bucket's tiles.
-template <class Rec>
-__device__ __forceinline__ void l2_scatter_slice(int qg, int kind, const L2Geom& G,
-                                                 const int* __restrict__ slice_base,
-                                                 const int* __restrict__ hist2,
-                                                 const Rec* __restrict__ tmp,
-                                                 const int* __restrict__ tmp_tile,
-                                                 Rec* __restrict__ rec, int* __restrict__ off,
-                                                 long long cap) {
-  extern __shared__ int h[];
-  const int nf_max = 1 << G.shift;
-  // first position of this kind
-  const long long kbase = hist2[(long long)nf_max * slice_base[kind * G.nb]];
-  const int cc = find_slice(slice_base, 2 * G.nb, qg);
-  const int q = qg - slice_base[cc], ns = slice_base[cc + 1] - slice_base[cc];
-  const int c = cc - kind * G.nb;
-  long long start, end;
-  bucket_range(G, cc, start, end);
-  const long long e0 = start + (long long)q * kSlice, e1 = min(min(e0 + kSlice, end), cap);
-  const int t0 = c << G.shift;
-  const int nf = (int)min((long long)nf_max, G.ntiles - t0);
-  const long long o = (long long)nf_max * slice_base[cc];
-  for (int f = threadIdx.x; f < nf_max; f += blockDim.x) {
-    const int v = (int)(hist2[o + (long long)f * ns + q] - kbase);
-    h[f] = v;
-    if (q == 0 && f < nf) off[t0 + f] = v;
-  }
-  __syncthreads();
-  // four entries per thread in flight: their tiles and records are loaded
-  // together, then ranked and stored
-  // (records as plain scalars: arrays of vector-type records would live in
-  // scratch)
-  constexpr int U = 4;
-  constexpr bool QUAD = std::is_same<Rec, double4>::value;
-  const long long stride = blockDim.x;
-  for (long long e = e0 + threadIdx.x; e < e1; e += U * stride) {
-    int tl[U] = {0, 0, 0, 0};
-    double rx[U] = {0.0, 0.0, 0.0, 0.0}, ry[U] = {0.0, 0.0, 0.0, 0.0},
-           rz[U] = {0.0, 0.0, 0.0, 0.0}, rw[U] = {0.0, 0.0, 0.0, 0.0};
-    int ri[U] = {0, 0, 0, 0};
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const long long eu = e + u * stride;
-      if (eu < e1) {
-        tl[u] = tmp_tile[eu];
-        if constexpr (QUAD) {
-          const double4 v = tmp[eu];
-          rx[u] = v.x;
-          ry[u] = v.y;
-          rz[u] = v.z;
-          rw[u] = v.w;
-        } else {
-          ri[u] = tmp[eu];
-        }
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      if (e + u * stride < e1) {
-        const int pos = atomicAdd(h + (tl[u] - t0), 1);
-        if (pos < cap) {
-          if constexpr (QUAD) rec[pos] = make_double4(rx[u], ry[u], rz[u], rw[u]);
-          else rec[pos] = ri[u];
-        }
-      }
-    }
-  }
-  __syncthreads();
-}
-
 // Per slice (both kinds in one launch): LDS cursors from the scanned hist2
-// place every entry at its final position, grouped by tile; slice 0 of a
-// bucket writes the offsets of the bucket's tiles.
+// place every entry's particle index at its final position, grouped by tile;
+// slice 0 of a bucket writes the offsets of the bucket's tiles.
 __global__ __launch_bounds__(256) void k_l2_scatter(L2Geom G, const int* __restrict__ slice_base,
                                                    const int* __restrict__ hist2,
-                                                   const double4* __restrict__ ctmp,
-                                                   const int* __restrict__ ctmp_tile,
-                                                   double4* __restrict__ crec,
-                                                   int* __restrict__ coff, long long ccap,
-                                                   const int* __restrict__ stmp,
-                                                   const int* __restrict__ stmp_tile,
-                                                   int* __restrict__ srec,
-                                                   int* __restrict__ soff, long long scap) {
-  const int split = slice_base[G.nb], total = slice_base[2 * G.nb];
+                                                   const int2* __restrict__ ctmp,
+                                                   int* __restrict__ cidx,
+                                                   int* __restrict__ coff,
+                                                   const int2* __restrict__ stmp,
+                                                   int* __restrict__ sidx,
+                                                   int* __restrict__ soff) {
+  extern __shared__ int h[];
+  const int nf_max = 1 << G.shift;
+  const int total = slice_base[2 * G.nb];
   for (int qg = blockIdx.x; qg < total; qg += gridDim.x) {
-    if (qg < split)
-      l2_scatter_slice<double4>(qg, 0, G, slice_base, hist2, ctmp, ctmp_tile, crec, coff, ccap);
-    else
-      l2_scatter_slice<int>(qg, 1, G, slice_base, hist2, stmp, stmp_tile, srec, soff, scap);
+    const int cc = find_slice(slice_base, 2 * G.nb, qg);
+    const int kind = cc >= G.nb, c = cc - kind * G.nb;
+    const int q = qg - slice_base[cc], ns = slice_base[cc + 1] - slice_base[cc];
+    const int2* tmp = kind ? stmp : ctmp;
+    int* rec = kind ? sidx : cidx;
+    int* off = kind ? soff : coff;
+    const long long cap = kind ? G.cap1 : G.cap0;
+    // first position of this kind
+    const long long kbase = hist2[(long long)nf_max * slice_base[kind * G.nb]];
+    long long start, end;
+    bucket_range(G, cc, start, end);
+    const long long e0 = start + (long long)q * kSlice, e1 = min(min(e0 + kSlice, end), cap);
+    const int t0 = c << G.shift;
+    const int nf = (int)min((long long)nf_max, G.ntiles - t0);
+    const long long o = (long long)nf_max * slice_base[cc];
+    for (int f = threadIdx.x; f < nf_max; f += blockDim.x) {
+      const int v = (int)(hist2[o + (long long)f * ns + q] - kbase);
+      h[f] = v;
+      if (q == 0 && f < nf) off[t0 + f] = v;
+    }
+    __syncthreads();
+    // eight entries per thread in flight: loaded together, then ranked and stored
+    constexpr int U = 8;
+    const long long stride = blockDim.x;
+    for (long long e = e0 + threadIdx.x; e < e1; e += U * stride) {
+      int2 v[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        v[u] = (e + u * stride < e1) ? tmp[e + u * stride] : make_int2(0, t0);
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        if (e + u * stride < e1) {
+          const int pos = atomicAdd(h + (v[u].y - t0), 1);
+          if (pos < cap) rec[pos] = v[u].x;
+        }
+      }
+    }
+    __syncthreads();
   }
 }
 
@@ -2943,6 +2934,7 @@ __device__ __forceinline__ int image_shift(int code, int a, int glo, int D) {
 template <int ACC, int TYZ, bool OWN>
 __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(7))) void k_tile_deposit(Mesh M, TileGrid T,
                                                       const int* __restrict__ coff,
+                                                      const int* __restrict__ cidx,
                                                       const double4* __restrict__ crec,
                                                       long long ccap,
                                                       const int* __restrict__ soff,
@@ -3094,7 +3086,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(7))) void 
       if (first) {
         // CIC entries
         for (long long e = e0 + threadIdx.x; e < e1; e += blockDim.x) {
-          const double4 CR = crec[e];
+          const double4 CR = crec[cidx[e]];
           const int h[3] = {(int)floor(CR.x), (int)floor(CR.y), (int)floor(CR.z)};
           auto add = [&](int i, int j, int k, auto v) {
             if constexpr (OWN) {
@@ -3442,7 +3434,7 @@ hipError_t launch_bin(const Mesh& M, const TileGrid& T, const Particles* cic,
 #define PMP_L1H(OWN)                                                                        \
   hipLaunchKernelGGL(k_l1_hist<OWN>, dim3(nbc + nbs), dim3(256), lds1, s, M, T,               \
                      has_c ? *cic : Particles{}, has_s ? *sn : Particles{}, S, nb, hc, nbc, hs, \
-                     nbs, (const SnPk*)bw.sn_pk)
+                     nbs, (const SnPk*)bw.sn_pk, bw.cic_rec)
     if (!T.owner) PMP_L1H(0);
     else if (M.own_start == nullptr) PMP_L1H(2);  // one box covers the domain
     else PMP_L1H(1);
@@ -3458,8 +3450,8 @@ hipError_t launch_bin(const Mesh& M, const TileGrid& T, const Particles* cic,
 #define PMP_L1S(OWN)                                                                        \
   hipLaunchKernelGGL(k_l1_scatter<OWN>, dim3(nbc + nbs), dim3(256), lds1, s, M, T,            \
                      has_c ? *cic : Particles{}, has_s ? *sn : Particles{}, S, nb, hc, nbc, hs, \
-                     nbs, bw.cic_tmp, bw.cic_tmp_tile, bw.cic_cap, (const SnPk*)bw.sn_pk,       \
-                     bw.sn_tmp, bw.sn_tmp_tile, bw.sn_cap)
+                     nbs, bw.cic_rec, bw.cic_tmp, bw.cic_cap, (const SnPk*)bw.sn_pk, bw.sn_tmp, \
+                     bw.sn_cap)
     if (!T.owner) PMP_L1S(0);
     else if (M.own_start == nullptr) PMP_L1S(2);
     else PMP_L1S(1);
@@ -3484,7 +3476,7 @@ hipError_t launch_bin(const Mesh& M, const TileGrid& T, const Particles* cic,
   const size_t lds2 = ((size_t)1 << S) * sizeof(int);
   const int grid2 = (int)std::min<long long>(bw.max_slices, (long long)M.num_cu * 8);
   hipLaunchKernelGGL(k_l2_hist, dim3(grid2), dim3(256), lds2, s, G, (const int*)bw.slice_base,
-                     (const int*)bw.cic_tmp_tile, (const int*)bw.sn_tmp_tile, bw.cic_cap,
+                     (const int2*)bw.cic_tmp, (const int2*)bw.sn_tmp, bw.cic_cap,
                      bw.sn_cap, bw.hist2);
   const int nblocks2 = (int)((n2 + kScanBlock - 1) / kScanBlock);
   hipLaunchKernelGGL(k_scan_local, dim3(nblocks2), dim3(kScanBlock), 0, s, bw.hist2, bw.hist2,
@@ -3492,10 +3484,8 @@ hipError_t launch_bin(const Mesh& M, const TileGrid& T, const Particles* cic,
   hipLaunchKernelGGL(k_scan_finish, dim3(nblocks2), dim3(kScanBlock), 0, s, bw.hist2,
                      (const int*)bw.block_sums2, n2, used, S);
   hipLaunchKernelGGL(k_l2_scatter, dim3(grid2), dim3(256), lds2, s, G, (const int*)bw.slice_base,
-                     (const int*)bw.hist2, (const double4*)bw.cic_tmp,
-                     (const int*)bw.cic_tmp_tile, bw.cic_rec, bw.cic_off, bw.cic_cap,
-                     (const int*)bw.sn_tmp, (const int*)bw.sn_tmp_tile, bw.sn_rec, bw.sn_off,
-                     bw.sn_cap);
+                     (const int*)bw.hist2, (const int2*)bw.cic_tmp, bw.cic_idx, bw.cic_off,
+                     (const int2*)bw.sn_tmp, bw.sn_rec, bw.sn_off);
   return hipGetLastError();
 }
 
@@ -3562,7 +3552,8 @@ hipError_t launch_tile_deposit(const Mesh& M, const TileGrid& T, const Particles
   if (grid > 0x7fffffffll) grid = 0x7fffffffll;
 #define PMP_TILE(ACC, TT, TYZ, OWN)                                                           \
   hipLaunchKernelGGL((k_tile_deposit<ACC, TYZ, OWN>), dim3((unsigned)grid), dim3(block), lds, \
-                     s, M, T, coff, (const double4*)bw.cic_rec, bw.cic_cap, soff,             \
+                     s, M, T, coff, (const int*)bw.cic_idx, (const double4*)bw.cic_rec,       \
+                     bw.cic_cap, soff,                                                        \
                      (const int*)bw.sn_rec, (const SnPk*)bw.sn_pk, bw.sn_cap, t.chunk_cic,    \
                      t.chunk_sn,                                                              \
                      (const int*)bw.heavy_base, (const int2*)bw.heavy_unit,                   \

@@ -32,3 +32,21 @@ def test_snr_kernel_sizes(B, orc, r_k, sub, acc):  # noqa: F811
     w = dataclasses.replace(w, name=f"snr_r{r_k}_s{sub}", ghost=17, snr=W._one_box(pts, f),
                             snr_params=dataclasses.replace(w.snr_params, r_k=r_k, sub=sub))
     check(B, orc, w, acc)
+
+
+@pytest.mark.parametrize("kind", ["cic", "sn"])
+@pytest.mark.parametrize("n", [1, 4095, 4096, 4097, 8193])
+def test_binning_slices(B, orc, n, kind):  # noqa: F811
+    """One tile's entries around the slice length of the second sorting level,
+    every other bucket empty, and one particle kind absent."""
+    from test_gpu_parity import check as check_deposit
+    rng = np.random.default_rng(n)
+    pos = 20.0 + 0.9 * rng.random((n, 3))
+    w = W.c2(nx=40, n_cic=1, n_sn=1, dtype=np.float64)
+    if kind == "cic":
+        w = dataclasses.replace(w, name=f"slice_cic_{n}", sn=None,
+                                cic=W._one_box(pos, W.cic_fields(rng, n)))
+    else:
+        w = dataclasses.replace(w, name=f"slice_sn_{n}", cic=None,
+                                sn=W._one_box(pos, W.sn_fields(n, 1.5)))
+    check_deposit(B, orc, w, "fix64", tuning={"deposit_path": 1, "tile_x": 16, "tile_yz": 8})
