@@ -206,6 +206,8 @@ struct pmp_ctx {
     M.ghost = ghost;
     for (int a = 0; a < 3; ++a) M.domain[a] = domain[a];
     M.V = V;
+    int e2;
+    M.vinv = std::frexp(V, &e2) == 0.5 && e2 > -500 && e2 < 500 ? 1.0 / V : 0.0;
     M.nfield = nfield;
     for (int f = 0; f < 6; ++f) M.slot[f] = slot[f];
     M.acc = acc;

@@ -65,6 +65,7 @@ struct Mesh {
   int ghost;
   int domain[3];
   double V;
+  double vinv;  // 1 / V where V is a power of two (the quotient is then exact), else 0
   int nfield;   // buffer channels present
   int slot[6];  // buffer slot of rho, px, py, pz, E, K, or -1 when absent
   int acc;    // pmp_acc_t
@@ -217,7 +218,7 @@ struct BinWork {
   // `partial` and the last one to finish combines them in chunk order
   int* heavy_base;      // [ntiles] first chunk slot of a split tile, or -1
   int* sink_flag;       // [ntiles] owner tiles with sinks: 1 where a sink kernel may reach
-  int2* heavy_unit;     // [slot_cap] (tile, chunk) of each slot; tile -1: unused
+  int4* heavy_unit;     // [slot_cap] (tile, chunk, chunks) of each slot; tile -1: unused
   int* heavy_count;     // [1] chunk slots claimed this step (may exceed slot_cap)
   int* arrive;          // [slot_cap] finished chunks, at the tile's first slot
   void* partial;        // [slot_cap][2][lcells] 8-byte partial sums

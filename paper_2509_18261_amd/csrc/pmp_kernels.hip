@@ -1659,9 +1659,10 @@ __global__ __launch_bounds__(kChunk) void k_fold(Mesh M, typename AccT<ACC>::T* 
 
 // ------------------------------------------------------------------ apply
 
-// Limiter counters of one thread, reduced per wavefront before the atomics.
+// Limiter counters of one thread (a thread meets far fewer than 2^32 cells),
+// reduced per wavefront before the atomics.
 struct ApplyCounts {
-  unsigned long long touched = 0, bind = 0, lam = 0, fall = 0;
+  unsigned touched = 0, bind = 0, lam = 0, fall = 0;
   bool bad = false;
 };
 
@@ -1738,42 +1739,66 @@ __device__ __forceinline__ double apply_cell(S* st, long long stride, double Dr,
 // with the same rounded operations: f = 1 - 0 / rho is exactly 1 for any
 // nonzero, non-NaN rho, so rho1 = rho + Dr, E1 = E + DE, the momentum is
 // unchanged (p + 0 squares to p^2), and the energy test reduces to
-// |p|^2 - 2 rho1 E1 (e_int >= 0 mode): lam = 1, or the floor.  A zero or
-// NaN rho, and the specific-e_int mode, take apply_cell itself.
+// |p|^2 - 2 rho1 (E1 - emin): lam = 1, or the floor.  A zero or NaN rho makes
+// f, and with it every field, NaN.
 template <class S>
-__device__ __forceinline__ void apply_cell_nosrc(S* st, long long stride, double Dr, double DE,
-                                                 const Limits& L, ApplyCounts& cnt) {
-  if (Dr == 0.0 && DE == 0.0) return;  // no update: the cell is left alone
-  const double rho = (double)st[0];
-  if (!(rho != 0.0 && rho == rho) || L.eint_mode != 0) {
-    apply_cell(st, stride, Dr, 0.0, 0.0, 0.0, DE, 0.0, L, cnt);
-    return;
-  }
-  const double px = (double)st[stride];
-  const double py = (double)st[2 * stride];
-  const double pz = (double)st[3 * stride];
-  const double E = (double)st[4 * stride];
+struct CellState {
+  S rho, px, py, pz, E;
+};
+template <class S>
+__device__ __forceinline__ CellState<S> load_cell(const S* st, long long stride) {
+  return {st[0], st[stride], st[2 * stride], st[3 * stride], st[4 * stride]};
+}
+template <class S>
+__device__ __forceinline__ void finish_cell_nosrc(S* st, long long stride,
+                                                  const CellState<S>& C, double Dr, double DE,
+                                                  const Limits& L, ApplyCounts& cnt) {
+  const double rho = (double)C.rho, px = (double)C.px, py = (double)C.py, pz = (double)C.pz,
+               E = (double)C.E;
+  const double pp = (px * px + py * py) + pz * pz;
   const double rho1 = rho + Dr;
   double E1 = E + DE;
-  const double Kc = (2.0 * rho1) * E1;
-  const double pp = (px * px + py * py) + pz * pz;
+  double emin = 0.0;
+  if (L.eint_mode == 1) {
+    const double eint0 = E - pp / (2.0 * rho);
+    emin = rho1 * (eint0 / rho);
+  }
+  const double Kc = (2.0 * rho1) * (E1 - emin);
   if (!(pp - Kc <= 0.0)) {
     // lam = 0: the kinetic part stays, e_int at its floor
-    E1 = 0.0 + pp / (2.0 * rho1);
+    E1 = emin + pp / (2.0 * rho1);
     ++cnt.fall;
     ++cnt.lam;
+  }
+  if (!(rho != 0.0 && rho == rho)) {
+    if (pp - Kc <= 0.0) {  // (rho = 0: f, and the test above with it, is NaN)
+      ++cnt.fall;
+      ++cnt.lam;
+    }
+    cnt.bad = true;
+    for (int a = 0; a < 5; ++a) st[a * stride] = (S)__builtin_nan("");
+    return;
   }
   if (!(rho > 0.0) || !isfinite(E1) || !isfinite(rho1)) cnt.bad = true;
   st[0] = (S)rho1;
   st[4 * stride] = (S)E1;
 }
+template <class S>
+__device__ __forceinline__ void apply_cell_nosrc(S* st, long long stride, double Dr, double DE,
+                                                 const Limits& L, ApplyCounts& cnt) {
+  if (Dr == 0.0 && DE == 0.0) return;  // no update: the cell is left alone
+  finish_cell_nosrc(st, stride, load_cell(st, stride), Dr, DE, L, cnt);
+}
 
 // One atomic per wavefront and counter (call from every lane of the wave).
 __device__ __forceinline__ void flush_counts(const Mesh& M, ApplyCounts& cnt) {
-  const unsigned long long touched = group_sum<kWave>(cnt.touched);
-  const unsigned long long bind = group_sum<kWave>(cnt.bind);
-  const unsigned long long lamc = group_sum<kWave>(cnt.lam);
-  const unsigned long long fall = group_sum<kWave>(cnt.fall);
+  // nothing to count in most wavefronts (the reductions are a chain of 30
+  // dependent 64-bit shuffles)
+  if (!__any((cnt.touched | cnt.bind | cnt.lam | cnt.fall) != 0 || cnt.bad)) return;
+  const unsigned long long touched = group_sum<kWave>((unsigned long long)cnt.touched);
+  const unsigned long long bind = group_sum<kWave>((unsigned long long)cnt.bind);
+  const unsigned long long lamc = group_sum<kWave>((unsigned long long)cnt.lam);
+  const unsigned long long fall = group_sum<kWave>((unsigned long long)cnt.fall);
   const unsigned long long nbad = group_sum<kWave>((unsigned long long)cnt.bad);
   if ((threadIdx.x & (kWave - 1)) == 0) {
     if (touched) atomicAdd(&M.status->touched, touched);
@@ -2828,44 +2853,30 @@ __device__ __forceinline__ int tile_chunks(long long nc, long long ns, int cc, i
   return (int)max(1ll, max(a, b));
 }
 
-// Entry range [e0, e1) of tile t in a sorted list (entries past the
-// capacity were never written: the fill flagged them).
-__device__ __forceinline__ void tile_entries(const int* off, long long cap, long long t,
-                                             long long& e0, long long& e1) {
-  e0 = 0;
-  e1 = 0;
-  if (off) {
-    e0 = min((long long)off[t], cap);
-    e1 = min((long long)off[t + 1], cap);
-  }
-}
-
 // One thread per tile: tiles with more entries than a chunk holds claim
-// consecutive chunk slots (when slots remain) and list their chunks.
+// consecutive chunk slots (when slots remain) and list their chunks (tile,
+// chunk, chunks).  The sorted lists hold no entry past the capacity.
 __global__ __launch_bounds__(256) void k_units(TileGrid T, const int* __restrict__ coff,
-                                              long long ccap, const int* __restrict__ soff,
-                                              long long scap, int cc, int cs,
+                                              const int* __restrict__ soff, int cc, int cs,
                                               int* __restrict__ heavy_base,
-                                              int2* __restrict__ heavy_unit,
+                                              int4* __restrict__ heavy_unit,
                                               int* __restrict__ heavy_count,
-                                              int* __restrict__ arrive, long long slot_cap) {
+                                              int* __restrict__ arrive, int slot_cap) {
   for (long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x; t < T.ntiles;
        t += (long long)gridDim.x * blockDim.x) {
-    long long c0, c1, s0, s1;
-    tile_entries(coff, ccap, t, c0, c1);
-    tile_entries(soff, scap, t, s0, s1);
-    const int chunks = tile_chunks(c1 - c0, s1 - s0, cc, cs);
+    const int nc = coff ? coff[t + 1] - coff[t] : 0, ns = soff ? soff[t + 1] - soff[t] : 0;
+    const int chunks = tile_chunks(nc, ns, cc, cs);
     int base = -1;
     if (chunks > 1) {
       const int b0 = atomicAdd(heavy_count, chunks);
       if ((long long)b0 + chunks <= slot_cap) {
         base = b0;
-        for (int j = 0; j < chunks; ++j) heavy_unit[b0 + j] = make_int2((int)t, j);
+        for (int j = 0; j < chunks; ++j) heavy_unit[b0 + j] = make_int4((int)t, j, chunks, 0);
         arrive[b0] = 0;
       } else {
         // out of slots: the tile stays whole; mark the slots it claimed unused
-        for (long long j = b0; j < min((long long)b0 + chunks, slot_cap); ++j)
-          heavy_unit[j] = make_int2(-1, 0);
+        for (long long j = b0; j < min((long long)b0 + chunks, (long long)slot_cap); ++j)
+          heavy_unit[j] = make_int4(-1, 0, 0, 0);
       }
     }
     heavy_base[t] = base;
@@ -2922,33 +2933,45 @@ __device__ __forceinline__ int image_shift(int code, int a, int glo, int D) {
 }
 
 // One workgroup per work unit (a whole tile, or one chunk of a split tile):
-// CIC entries one per thread; supernovae in batches of up to one wavefront:
-// one lane per entry gathers its particle's record, clips the sphere's
-// candidate rows to the tile and adds the fixed-point remainder; then one
-// thread per (entry, tile row) finds the row's member run with the exact row
-// test and adds it.  Every addition goes to the LDS accumulators.  Then every present channel of every cell of the
-// tile is stored once (channels without sources as zero).  Membership,
-// shares and fixed-point remainders are the same as in the direct kernels.
-// (7 waves per SIMD: the register budget that keeps the LDS-limited
-// occupancy of the common tile shapes without spilling)
-template <int ACC, int TYZ, bool OWN>
-__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(7))) void k_tile_deposit(Mesh M, TileGrid T,
+// CIC entries one per thread; then supernovae in batches of up to one
+// wavefront: one lane per entry gathers its particle's record, clips the
+// sphere's candidate rows to the tile and adds the fixed-point remainder; then
+// one thread per (entry, tile row) finds the row's member run with the exact
+// row test and adds it.  Every addition goes to the LDS accumulators.  Then
+// every present channel of every cell of the tile is stored once (channels
+// without sources as zero), or, on owner tiles, every cell with an update is
+// applied.  Membership, shares and fixed-point remainders are the same as in
+// the direct kernels.
+//
+// What bounds it: with FP64 state the state's cache lines (512^3 FP64 moves
+// 6 GB in 1480 us, 4.1 TB/s; a kernel that only streams such a masked state
+// takes 1220 us); otherwise the latency of a tile's phases (metadata 1.9 us,
+// record gather 3.6, supernova rows 1.8, apply 5 of the 13 us of a 4096-box
+// tile), so what counts is resident wavefronts and loads in flight.  Hence
+// one instantiation per state type, 32-bit entry indices, one source-free
+// apply without the general one behind it and a CIC stencil in per-axis
+// tile-local indices (82 -> 71 registers), budgets of 6 or 7 wavefronts per
+// SIMD that hold without spilling (a spilled variant of the fixed-point pass
+// takes 1650 us, this one 1165), the states of several cells loaded together,
+// and the two record gathers on different wavefronts.  Tile pass before and
+// after: 4096 boxes FP32 1400 -> 1110 us, 512^3 fixed point over FP32 1490 ->
+// 1165, 512 boxes FP64 with sinks 183 -> 161, 256^3 FP64 clustered 137 -> 119.
+template <int ACC, int TYZ, bool OWN, class ST>
+__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(ACC == PMP_ACC_FIX64 && sizeof(ST) == 4 ? 7 : 6))) void k_tile_deposit(Mesh M, TileGrid T,
                                                       const int* __restrict__ coff,
                                                       const int* __restrict__ cidx,
                                                       const double4* __restrict__ crec,
-                                                      long long ccap,
                                                       const int* __restrict__ soff,
                                                       const int* __restrict__ sidx,
                                                       const SnPk* __restrict__ pk,
-                                                      long long scap, int cc, int cs,
                                                       const int* __restrict__ heavy_base,
-                                                      const int2* __restrict__ heavy_unit,
+                                                      const int4* __restrict__ heavy_unit,
                                                       const int* __restrict__ heavy_count,
                                                       int* __restrict__ arrive,
                                                       void* __restrict__ partial_v,
-                                                      long long slot_cap,
+                                                      int slot_cap,
                                                       typename AccT<ACC>::T* __restrict__ buf,
-                                                      void* __restrict__ state, Limits L,
+                                                      ST* __restrict__ state, Limits L,
                                                       const int* __restrict__ sink_flag) {
   using OutT = typename AccT<ACC>::T;
   constexpr bool FIXED = (ACC == PMP_ACC_FIX64);
@@ -2975,33 +2998,41 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(7))) void 
   double* eb0 = reinterpret_cast<double*>(a4 + lcells);
   double* eb4 = eb0 + lcells;
   // the current batch of the tile's supernovae
+  static_assert(kTileSnBatch <= kWave && sizeof(SnTile) % 16 == 0,
+                "one batch entry per lane of a wave");
   constexpr int NB = kTileSnBatch;
-  static_assert(NB <= kWave && sizeof(SnTile) % 16 == 0, "one batch entry per lane of a wave");
   SnTile* bent = reinterpret_cast<SnTile*>(BOUNDS ? reinterpret_cast<LT*>(eb4 + lcells)
                                                    : a4 + lcells);
-  // work units: the chunks of split tiles first (the longest units), then
-  // every other tile whole, in tile order
-  const long long nheavy = min((long long)*heavy_count, slot_cap);
-  for (long long unit = blockIdx.x; unit < T.ntiles + nheavy; unit += gridDim.x) {
-    int tile;
-    int chunk = 0, base = -1;
-    if (unit < nheavy) {
-      const int2 hu = heavy_unit[unit];
+  // work units: the chunk slots of split tiles first (the longest units),
+  // then every other tile whole, in tile order (the slots keep their number
+  // whether claimed or not, so that a tile's number depends on no load)
+  const int nunits = (int)T.ntiles + slot_cap;
+  for (int unit = blockIdx.x; unit < nunits; unit += gridDim.x) {
+    int tile = unit - slot_cap;
+    int chunk = 0, chunks = 1, base = -1;
+    if (tile < 0) {
+      if (unit >= *heavy_count) continue;
+      const int4 hu = heavy_unit[unit];
       if (hu.x < 0) continue;
       tile = hu.x;
       chunk = hu.y;
-      base = heavy_base[tile];
-    } else {
-      tile = (int)(unit - nheavy);
+      chunks = hu.z;
+      base = unit - chunk;
     }
     // the tile's metadata, loaded together; a tile split into chunks is
     // done by its chunk units
     const int hb = heavy_base[tile];
     const TileGeo G = T.geo[tile];
-    long long e0, e1, s0, s1;
-    tile_entries(coff, ccap, tile, e0, e1);
-    tile_entries(soff, scap, tile, s0, s1);
-    if (unit >= nheavy && hb >= 0) continue;
+    int e0 = 0, e1 = 0, s0 = 0, s1 = 0;
+    if (coff) {
+      e0 = coff[tile];
+      e1 = coff[tile + 1];
+    }
+    if (soff) {
+      s0 = soff[tile];
+      s1 = soff[tile + 1];
+    }
+    if (base < 0 && hb >= 0) continue;
     for (int c = threadIdx.x; c < lcells; c += blockDim.x) {
       a0[c] = (LT)0;
       a4[c] = (LT)0;
@@ -3010,26 +3041,98 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(7))) void 
         eb4[c] = 0.0;
       }
     }
-    int chunks = 1;
+    // owner tiles: every contribution to the tile's cells is in its lists, so
+    // with empty lists no cell changes (a tile kept for the sinks is stored)
+    if (OWN && e0 == e1 && s0 == s1 && state && !(sink_flag && sink_flag[tile])) continue;
     if (base >= 0) {
       // this chunk's share of the tile's entries
-      chunks = tile_chunks(e1 - e0, s1 - s0, cc, cs);
       const long long nc = e1 - e0, ns = s1 - s0;
-      e1 = e0 + nc * (chunk + 1) / chunks;
-      e0 = e0 + nc * chunk / chunks;
-      s1 = s0 + ns * (chunk + 1) / chunks;
-      s0 = s0 + ns * chunk / chunks;
+      e1 = e0 + (int)(nc * (chunk + 1) / chunks);
+      e0 = e0 + (int)(nc * chunk / chunks);
+      s1 = s0 + (int)(ns * (chunk + 1) / chunks);
+      s0 = s0 + (int)(ns * chunk / chunks);
     }
     __syncthreads();
     bool ovf = false;
-    long long spos = s0;
-    bool first = true;
-    while (first || spos < s1) {
-      // the batch's supernovae, one lane of the first wavefront each
-      const int nq = (int)min((long long)NB, s1 - spos);
-      if (threadIdx.x < kWave) {
-        const int q = threadIdx.x;
-        if (q < nq) {
+    // CIC entries, one per thread
+    for (int e = e0 + (int)threadIdx.x; e < e1; e += blockDim.x) {
+      const double4 CR = crec[cidx[e]];
+      // per axis the stencil's two cells as tile-local indices (-1: not in
+      // the tile, or no weight there), and the second cell's weight
+      int l0[3], l1[3], lh[3];
+      double f[3];
+      const double pos[3] = {CR.x, CR.y, CR.z};
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        const double t = pos[a] - 0.5, fl = floor(t);
+        f[a] = t - fl;
+        const int i = (int)fl;
+        auto local = [&](int c) {
+          if constexpr (OWN) c = wrap_once(c, M.domain[a]);  // the periodic image
+          const int u = c - G.glo[a];
+          return (unsigned)u < (unsigned)G.ext[a] ? u : -1;
+        };
+        l0[a] = local(i);
+        const int second = local(i + 1);
+        lh[a] = (int)floor(pos[a]) == i ? l0[a] : second;
+        l1[a] = f[a] == 0.0 ? -1 : second;
+      }
+      // (m wx) wy of the four rows along z, then times wz and over V, the
+      // products and their order as in cic_one
+      const double mx[2] = {CR.w * (1.0 - f[0]), CR.w * f[0]};
+      long long qsum = 0;
+      bool okc = true;
+#pragma unroll 1
+      for (int dk = 0; dk < 2; ++dk) {
+        const double wz = dk ? f[2] : 1.0 - f[2];
+        const int lw = dk ? l1[2] : l0[2];
+        if (!FIXED && lw < 0) continue;
+        auto corner = [&](int dj, int di) {
+          const int lv = dj ? l1[1] : l0[1], lu = di ? l1[0] : l0[0];
+          double c = ((di ? mx[1] : mx[0]) * (dj ? f[1] : 1.0 - f[1])) * wz;
+          c = M.vinv != 0.0 ? c * M.vinv : c / M.V;
+          const int lc = (lw * TY + lv) * TXP + lu;
+          if constexpr (FIXED) {
+            long long q;
+            if (!quantise(c, q)) { okc = false; return; }
+            qsum += q;
+            if ((lu | lv | lw) >= 0) lds_add(a0 + lc, q);
+          } else {
+            if ((lu | lv) < 0) return;
+            if constexpr (BOUNDS) lds_add_b(a0 + lc, eb0 + lc, c);
+            else lds_add(a0 + lc, c);
+          }
+        };
+        if constexpr (FIXED) {
+          // one corner at a time: the conversions to the 2^-40 grid would
+          // otherwise hold 20 registers more
+#pragma unroll 1
+          for (int q = 0; q < 4; ++q) corner(q >> 1, q & 1);
+        } else {
+#pragma unroll
+          for (int q = 0; q < 4; ++q) corner(q >> 1, q & 1);
+        }
+      }
+      if constexpr (FIXED) {
+        // the rounding residue of the particle's total, to its host cell
+        long long Q;
+        const double tot = M.vinv != 0.0 ? CR.w * M.vinv : CR.w / M.V;
+        if (okc && quantise(tot, Q)) {
+          if ((lh[0] | lh[1] | lh[2]) >= 0)
+            lds_add(a0 + (lh[2] * TY + lh[1]) * TXP + lh[0], Q - qsum);
+        } else {
+          ovf = true;
+        }
+      }
+    }
+    for (int spos = s0; spos < s1; spos += NB) {
+      // the batch's supernovae, one lane of the last wavefront each (the CIC
+      // entries above start on the first, so that both chains of dependent
+      // loads, index then record, run side by side in most tiles)
+      const int nq = min(NB, s1 - spos);
+      {
+        const int q = (int)threadIdx.x - (int)blockDim.x + kWave;
+        if (q >= 0 && q < nq) {
           const SnPk& R = pk[sidx[spos + q]];
           Sphere Sp;
           sphere_init(Sp, R.x, R.y, R.z, R.r);
@@ -3083,30 +3186,6 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(7))) void 
           }
         }
       }
-      if (first) {
-        // CIC entries
-        for (long long e = e0 + threadIdx.x; e < e1; e += blockDim.x) {
-          const double4 CR = crec[cidx[e]];
-          const int h[3] = {(int)floor(CR.x), (int)floor(CR.y), (int)floor(CR.z)};
-          auto add = [&](int i, int j, int k, auto v) {
-            if constexpr (OWN) {
-              // owner tiles: the cell's periodic image
-              i = wrap_once(i, M.domain[0]);
-              j = wrap_once(j, M.domain[1]);
-              k = wrap_once(k, M.domain[2]);
-            }
-            const int u = i - G.glo[0], vv = j - G.glo[1], w = k - G.glo[2];
-            if ((unsigned)u < (unsigned)G.ext[0] && (unsigned)vv < (unsigned)G.ext[1] &&
-                (unsigned)w < (unsigned)G.ext[2]) {
-              const int lc = (w * TY + vv) * TXP + u;
-              if constexpr (BOUNDS) lds_add_b(a0 + lc, eb0 + lc, v);
-              else lds_add(a0 + lc, v);
-            }
-          };
-          if (!cic_one<FIXED>(CR.x, CR.y, CR.z, CR.w, M.V, h, add)) ovf = true;
-        }
-        first = false;
-      }
       __syncthreads();
       // supernova rows: the member run of tile row (v, w), clipped to the tile
       for (int it = threadIdx.x; it < (nq << SSH); it += blockDim.x) {
@@ -3158,7 +3237,6 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(7))) void 
           }
         }
       }
-      spos += nq;
       __syncthreads();
     }
     if (ovf) raise_flag(M.status, PMP_FLAG_OVERFLOW);
@@ -3208,6 +3286,45 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(7))) void 
     const int ox0 = G.o[0] - g, oy0 = G.o[1] - g, oz0 = G.o[2] - g;
     const long long tso = G.soff + ((long long)oz0 * n1 + oy0) * n0 + ox0;
     const long long tbo = ((long long)G.o[2] * G.p[1] + G.o[1]) * G.p[0] + G.o[0];
+    if (OWN && apply_here) {
+      // the states of UN cells per thread are loaded together, then each is
+      // finished and stored, so that one memory latency serves them all (rows
+      // are TX = 2^k cells).  UN is what the register budget holds without
+      // spilling: four cells of an FP64 state spill and cost 24% (512^3 FP64:
+      // 1835 against 1480 us), two of an FP32 state 4% more than four
+      constexpr int UN = (sizeof(ST) == 4 && !FIXED) ? 4 : 2;
+      const int tsx = T.ts[0];
+      for (int c = threadIdx.x; c < tcells; c += UN * blockDim.x) {
+        CellState<ST> in[UN];
+        int off[UN];  // cell's offset from the tile's first; -1: outside, or no update
+#pragma unroll
+        for (int k = 0; k < UN; ++k) {
+          const int ck = c + k * (int)blockDim.x;
+          const int u = ck & (TX - 1), row = ck >> tsx, v = row & (TY - 1), w = row >> YSH;
+          off[k] = -1;
+          if (ck < tcells && u < G.ext[0] && v < G.ext[1] && w < G.ext[2]) {
+            const int lc = row * TXP + u;
+            const OutT r = sr >= 0 ? from_lds<OutT>(a0[lc]) : (OutT)0;
+            const OutT e = se >= 0 ? from_lds<OutT>(a4[lc]) : (OutT)0;
+            if (r != (OutT)0 || e != (OutT)0) {
+              off[k] = (w * n1 + v) * n0 + u;
+              in[k] = load_cell((const ST*)state + (tso + off[k]), ncell);
+            }
+          }
+        }
+#pragma unroll
+        for (int k = 0; k < UN; ++k) {
+          if (off[k] < 0) continue;
+          const int ck = c + k * (int)blockDim.x;
+          const int lc = (ck >> tsx) * TXP + (ck & (TX - 1));
+          const double Dr = sr >= 0 ? to_f64(from_lds<OutT>(a0[lc])) : 0.0;
+          const double DE = se >= 0 ? to_f64(from_lds<OutT>(a4[lc])) : 0.0;
+          finish_cell_nosrc(state + (tso + off[k]), ncell, in[k], Dr, DE, L, cnt);
+        }
+      }
+      __syncthreads();
+      continue;
+    }
     // cell c = u + TX row of the LDS tile, advanced by blockDim per step
     const int drow = small_div((int)blockDim.x, TX, inv_tx), du = (int)blockDim.x - drow * TX;
     int row = small_div((int)threadIdx.x, TX, inv_tx);
@@ -3228,13 +3345,10 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(7))) void 
         // (with owner tiles every cell is owned and its sum complete: applied,
         // or, in a step with sinks, stored for the sink passes and the apply)
         const int ox = ox0 + u, oy = oy0 + v, oz = oz0 + w;
-        if (apply_here && (OWN || (ox >= g && ox < n0 - g && oy >= g && oy < n1 - g &&
-                                   oz >= g && oz < n2 - g))) {
+        if (!OWN && apply_here && ox >= g && ox < n0 - g && oy >= g && oy < n1 - g && oz >= g &&
+            oz < n2 - g) {
           const long long si = tso + ((w * n1 + v) * n0 + u);
-          if (M.state == PMP_STATE_F32)
-            apply_cell_nosrc((float*)state + si, ncell, to_f64(vr), to_f64(ve), L, cnt);
-          else
-            apply_cell_nosrc((double*)state + si, ncell, to_f64(vr), to_f64(ve), L, cnt);
+          apply_cell_nosrc(state + si, ncell, to_f64(vr), to_f64(ve), L, cnt);
         } else {
           const long long idx = tbo + ((w * G.p[1] + v) * G.p[0] + u);
           for (int f = 0; f < M.nfield; ++f) {
@@ -3495,12 +3609,12 @@ hipError_t launch_tile_prep(const Mesh& M, const TileGrid& T, const Particles* c
   const int* coff = (cic && cic->n > 0) ? bw.cic_off : nullptr;
   const int* soff = (sn && sn->n > 0) ? bw.sn_off : nullptr;
   hipLaunchKernelGGL(k_units, dim3(grid_for(T.ntiles, 256, M.num_cu * 16)), dim3(256), 0, s, T,
-                     coff, bw.cic_cap, soff, bw.sn_cap,
+                     coff, soff,
                      // the reproducibility mode never splits a tile: each tile
                      // sums all of its cells' contributions (and their bounds)
                      M.acc == PMP_ACC_F64R ? 0x7fffffff : t.chunk_cic,
                      M.acc == PMP_ACC_F64R ? 0x7fffffff : t.chunk_sn, bw.heavy_base,
-                     bw.heavy_unit, bw.heavy_count, bw.arrive, bw.slot_cap);
+                     bw.heavy_unit, bw.heavy_count, bw.arrive, (int)bw.slot_cap);
   return hipGetLastError();
 }
 
@@ -3545,20 +3659,22 @@ hipError_t launch_tile_deposit(const Mesh& M, const TileGrid& T, const Particles
   const int* soff = (sn && sn->n > 0) ? bw.sn_off : nullptr;
   const int block = t.tile_block;
   const size_t lds = (size_t)tile_lds_bytes_wx(T.wx, T.t[1], M.acc == PMP_ACC_F64R);
-  long long grid = T.ntiles;
+  long long grid = T.ntiles + bw.slot_cap;
   if (t.tile_grid_per_cu > 0)
     grid = std::min<long long>(grid, (long long)M.num_cu * t.tile_grid_per_cu);
   if (grid < 1) grid = 1;
   if (grid > 0x7fffffffll) grid = 0x7fffffffll;
-#define PMP_TILE(ACC, TT, TYZ, OWN)                                                           \
-  hipLaunchKernelGGL((k_tile_deposit<ACC, TYZ, OWN>), dim3((unsigned)grid), dim3(block), lds, \
-                     s, M, T, coff, (const int*)bw.cic_idx, (const double4*)bw.cic_rec,       \
-                     bw.cic_cap, soff,                                                        \
-                     (const int*)bw.sn_rec, (const SnPk*)bw.sn_pk, bw.sn_cap, t.chunk_cic,    \
-                     t.chunk_sn,                                                              \
-                     (const int*)bw.heavy_base, (const int2*)bw.heavy_unit,                   \
-                     (const int*)bw.heavy_count, bw.arrive, bw.partial, bw.slot_cap,          \
-                     (TT*)buf, state, L, sink_flag)
+  const bool f32 = M.state == PMP_STATE_F32;
+#define PMP_TILE_S(ACC, TT, TYZ, OWN, ST)                                                     \
+  hipLaunchKernelGGL((k_tile_deposit<ACC, TYZ, OWN, ST>), dim3((unsigned)grid), dim3(block),  \
+                     lds, s, M, T, coff, (const int*)bw.cic_idx, (const double4*)bw.cic_rec,  \
+                     soff, (const int*)bw.sn_rec, (const SnPk*)bw.sn_pk,                      \
+                     (const int*)bw.heavy_base, (const int4*)bw.heavy_unit,                   \
+                     (const int*)bw.heavy_count, bw.arrive, bw.partial, (int)bw.slot_cap,     \
+                     (TT*)buf, (ST*)state, L, sink_flag)
+#define PMP_TILE(ACC, TT, TYZ, OWN)                        \
+  if (f32) PMP_TILE_S(ACC, TT, TYZ, OWN, float);           \
+  else PMP_TILE_S(ACC, TT, TYZ, OWN, double)
   // owner tiles: no reproducibility-mode variant (its bounds need the fold's order)
 #define PMP_TILE_ACC(TYZ)                                                       \
   if (T.owner) {                                                                \
@@ -3582,6 +3698,7 @@ hipError_t launch_tile_deposit(const Mesh& M, const TileGrid& T, const Particles
   }
 #undef PMP_TILE_ACC
 #undef PMP_TILE
+#undef PMP_TILE_S
   return hipGetLastError();
 }
 
