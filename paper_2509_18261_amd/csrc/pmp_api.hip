@@ -693,7 +693,7 @@ template <class T> int regrow(T** p, long long have, long long need) {
 // Sizes (elements) of the binned-deposit scratch arrays for these particle
 // counts and the current tiles.
 struct BinSizes {
-  int shift = 0, nb = 0;
+  int shift = 0, nb = 0, sn_slots = 1;
   long long hist = 0, blocks = 0, tiles1 = 0, partial = 0, slot_cap = 0, cic_cap = 0,
             sn_cap = 0, hist2 = 0, blocks2 = 0, slice_base = 0, n_sn = 0, n_cic = 0;
 };
@@ -730,6 +730,7 @@ int bin_sizes(const pmp_ctx* c, long long n_cic, long long n_sn, double r_max, B
   const long long nbs = (n_sn + kBinChunkSn - 1) / kBinChunkSn;
   const long long cic_cap = std::max<long long>(8 * n_cic, 1);
   const long long sn_cap = std::max<long long>(maxt * n_sn, 1);
+  z.sn_slots = (int)std::min<long long>(maxt, 1 << 30);
   const long long full_slices = (cic_cap + kSlice - 1) / kSlice + (sn_cap + kSlice - 1) / kSlice;
   // coarse buckets of 2^shift consecutive tiles: at most 512 buckets, or 1024
   // where that would put more than 256 tiles in one (sized for the padded
@@ -804,6 +805,7 @@ size_t carve_bin(const BinSizes& z, char* base, BinWork* w) {
     W.sn_cap = z.sn_cap;
     W.slot_cap = z.slot_cap;
     W.shift = z.shift;
+    W.sn_slots = z.sn_slots;
     W.nbuckets = z.nb;
     W.max_slices = (z.hist2 - 1) >> z.shift;
   }
@@ -832,6 +834,7 @@ int ensure_bin_work(pmp_ctx* c, long long n_cic, long long n_sn, double r_max, h
   const long long slot_cap = z.slot_cap, partial = z.partial, cic_cap = z.cic_cap,
                   sn_cap = z.sn_cap;
   c->bw.shift = shift;
+  c->bw.sn_slots = z.sn_slots;
   c->bw.nbuckets = nb;
   const bool grow = hist > c->bw_hist || blocks > c->bw_blocks || c->ntiles + 1 > c->bw_tiles ||
                     cic_cap > c->bw.cic_cap || sn_cap > c->bw.sn_cap || n_sn > c->bw_nsn ||
@@ -1127,10 +1130,8 @@ int do_deposit(pmp_ctx* c, void* buf, const void* state, const pmp_cic* cic, con
     const bool flagged = owner && has_sink && fuse_state;
     {
       PhaseTimer t(c, PMP_PHASE_BIN, s);
-      PMP_HIP(launch_bin(M, T, has_cic ? &pc : nullptr, has_sn ? &ps : nullptr, c->bw,
-                         c->tune.count_lanes, s));
-      PMP_HIP(launch_tile_prep(M, T, has_cic ? &pc : nullptr, has_sn ? &ps : nullptr, c->bw,
-                               c->tune, s));
+      PMP_HIP(launch_bin(M, T, has_cic ? &pc : nullptr, has_sn ? &ps : nullptr, c->bw, c->tune,
+                         s));
       if (flagged)
         PMP_HIP(launch_sink_tiles(M, T, from_sinks(sinks), sinks->r_k, c->bw.sink_flag, s));
     }

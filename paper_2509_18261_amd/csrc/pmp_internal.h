@@ -207,6 +207,7 @@ struct BinWork {
   int* sn_rec;           // sorted by tile: particle index
   int* sn_off;          // [ntiles + 1]
   SnPk* sn_pk;          // [n_sn]
+  int sn_slots;         // entry capacity per supernova: the most tiles one can touch
   long long cic_cap, sn_cap;
   // level 2 works on slices of at most kSlice records of one bucket
   int* slice_base;      // [2 * nbuckets + 1]: first slice of each (kind, bucket)
@@ -226,6 +227,13 @@ struct BinWork {
 };
 
 constexpr int kSlice = 4096;
+// Deposits sorted by k_small_count: at most this many tiles (an LDS histogram
+// of 32 KB) and CIC particles plus 8 per supernova.  Beyond that the two-level
+// sort is as fast: whole steps at 128^3 FP64 take 80 us with this sort and 91
+// with the other for 100000 CIC particles and 10000 supernovae, 107 and 100
+// for twice as many, 82 and 81 for 200000 CIC particles alone.
+constexpr long long kSmallTiles = 8192;
+constexpr long long kSmallEntries = 200000;
 
 // Supernova entries per batch of the tile pass: one per lane of a wavefront.
 constexpr int kTileSnBatch = 64;
@@ -253,12 +261,9 @@ hipError_t launch_cic_direct(const Mesh& M, const Particles& P, void* buf, int b
 // workgroup per tile accumulates in LDS and stores every field of its cells.
 // cic or sn may be null.  Replaces the zero fill.  phase_bin/phase_tile
 // bracket the two halves for the profiler.
+// (the sort, and the chunk table of split tiles)
 hipError_t launch_bin(const Mesh& M, const TileGrid& T, const Particles* cic,
-                      const Particles* sn, BinWork& bw, int count_lanes, hipStream_t s);
-// Supernova tile records and the chunk table of split tiles (after launch_bin).
-hipError_t launch_tile_prep(const Mesh& M, const TileGrid& T, const Particles* cic,
-                            const Particles* sn, const BinWork& bw, const pmp_tuning& t,
-                            hipStream_t s);
+                      const Particles* sn, BinWork& bw, const pmp_tuning& t, hipStream_t s);
 // state non-null: the step's Steps 3 + 5 are fused in for owned cells at
 // least g from every face of their box (no ghost image reaches them); those
 // cells' buffer entries are left unwritten, and launch_fold_apply finishes

@@ -38,15 +38,40 @@ def test_snr_kernel_sizes(B, orc, r_k, sub, acc):  # noqa: F811
 @pytest.mark.parametrize("n", [1, 4095, 4096, 4097, 8193])
 def test_binning_slices(B, orc, n, kind):  # noqa: F811
     """One tile's entries around the slice length of the second sorting level,
-    every other bucket empty, and one particle kind absent."""
+    every other bucket empty, and one particle kind absent (more tiles than
+    the sort of small deposits takes)."""
     from test_gpu_parity import check as check_deposit
     rng = np.random.default_rng(n)
     pos = 20.0 + 0.9 * rng.random((n, 3))
-    w = W.c2(nx=40, n_cic=1, n_sn=1, dtype=np.float64)
+    w = W.c2(nx=80, n_cic=1, n_sn=1, dtype=np.float64)
     if kind == "cic":
         w = dataclasses.replace(w, name=f"slice_cic_{n}", sn=None,
                                 cic=W._one_box(pos, W.cic_fields(rng, n)))
     else:
         w = dataclasses.replace(w, name=f"slice_sn_{n}", cic=None,
                                 sn=W._one_box(pos, W.sn_fields(n, 1.5)))
-    check_deposit(B, orc, w, "fix64", tuning={"deposit_path": 1, "tile_x": 16, "tile_yz": 8})
+    check_deposit(B, orc, w, "fix64", tuning={"deposit_path": 1, "tile_x": 16, "tile_yz": 2})
+
+
+@pytest.mark.parametrize("fuse", [0, 2])
+@pytest.mark.parametrize("n_cic,n_sn,nx,tile", [
+    (0, 1, 24, (16, 8)), (1, 0, 24, (16, 8)), (256, 64, 40, (64, 4)), (257, 65, 40, (32, 2)),
+    (5000, 1025, 61, (16, 2)), (12000, 2000, 62, (16, 2)),   # 3844 to 8192 and more tiles
+    (199992, 1, 33, (32, 4)), (199993, 1, 33, (32, 4)),      # either side of the entry limit
+    (100000, 100, 96, (16, 4)),
+])
+def test_sort_of_small_deposits(B, orc, n_cic, n_sn, nx, tile, fuse):  # noqa: F811
+    """Deposits on either side of the rule that sends a sort to the short
+    launches (8192 tiles, 200000 entries), around the block sizes of its
+    kernels, on uneven boxes too, and with tiles split into chunks."""
+    from test_gpu_parity import step_vs_oracle
+    rng = np.random.default_rng(n_cic + n_sn + nx)
+    edges = ([nx], [nx], [nx]) if nx % 2 == 0 else ([nx // 3, nx - nx // 3], [nx],
+                                                     [nx // 2, nx - nx // 2])
+    dom = (nx, nx, nx)
+    pc = W.clumped_positions(rng, n_cic, dom, nclump=2, a=3.0) if n_cic else None
+    ps = W.uniform_positions(rng, n_sn, dom) if n_sn else None
+    w = W.multibox(*edges, 4, positions_cic=pc, positions_sn=ps, sn_radius=3.0, seed=nx)
+    step_vs_oracle(B, orc, w, "fix64",
+                   tuning=dict(deposit_path=1, tile_x=tile[0], tile_yz=tile[1], chunk_cic=1024,
+                               chunk_sn=64, fuse_apply=fuse))
