@@ -2860,10 +2860,24 @@ __global__ __launch_bounds__(256) void k_l2_scatter(L2Geom G, const int* __restr
 }
 
 // Chunks a tile's entries are split into: at most cc CIC and cs supernova
-// entries per chunk.
-__device__ __forceinline__ int tile_chunks(long long nc, long long ns, int cc, int cs) {
-  const long long a = (nc + cc - 1) / cc, b = (ns + cs - 1) / cs;
-  return (int)max(1ll, max(a, b));
+// entries per chunk, and no more than a workgroup's share of the deposit's
+// nct and nst entries (total / share, but at least kChunkMin entries; up to
+// kChunksMost chunks on that account), so that a cluster's core, which may
+// hold a fifth of all particles in one tile, is spread over the chip.  1e6
+// Plummer particles at 256^3 FP64 on 16 x 8 x 8 tiles with cc = 16384: the step
+// with 256 sinks takes 270 us with whole chunks of cc behind device-scope
+// fences, 230 us without the fences (see the partial sums in the tile pass),
+// 202 us with the share; shares of one, two or four workgroups per compute
+// unit differ by 3%.
+constexpr int kChunkMinCic = 1024, kChunkMinSn = 128, kChunksMost = 32;
+__device__ __forceinline__ int tile_chunks(long long nc, long long ns, int cc, int cs,
+                                           long long nct, long long nst, int share) {
+  if (share <= 0) return 1;  // never split
+  const long long ec = max((long long)kChunkMinCic, nct / share);
+  const long long es = max((long long)kChunkMinSn, nst / share);
+  const long long want = min(max((nc + ec - 1) / ec, (ns + es - 1) / es), (long long)kChunksMost);
+  const long long need = max((nc + cc - 1) / cc, (ns + cs - 1) / cs);
+  return (int)max(1ll, max(want, need));
 }
 
 // One thread per tile: tiles with more entries than a chunk holds claim
@@ -2871,14 +2885,15 @@ __device__ __forceinline__ int tile_chunks(long long nc, long long ns, int cc, i
 // chunk, chunks).  The sorted lists hold no entry past the capacity.
 __global__ __launch_bounds__(256) void k_units(TileGrid T, const int* __restrict__ coff,
                                               const int* __restrict__ soff, int cc, int cs,
-                                              int* __restrict__ heavy_base,
+                                              int share, int* __restrict__ heavy_base,
                                               int4* __restrict__ heavy_unit,
                                               int* __restrict__ heavy_count,
                                               int* __restrict__ arrive, int slot_cap) {
+  const int nct = coff ? coff[T.ntiles] : 0, nst = soff ? soff[T.ntiles] : 0;
   for (long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x; t < T.ntiles;
        t += (long long)gridDim.x * blockDim.x) {
     const int nc = coff ? coff[t + 1] - coff[t] : 0, ns = soff ? soff[t + 1] - soff[t] : 0;
-    const int chunks = tile_chunks(nc, ns, cc, cs);
+    const int chunks = tile_chunks(nc, ns, cc, cs, nct, nst, share);
     int base = -1;
     if (chunks > 1) {
       const int b0 = atomicAdd(heavy_count, chunks);
@@ -2988,7 +3003,7 @@ __global__ __launch_bounds__(256) void k_small_count(Mesh M, TileGrid T, Particl
 __global__ __launch_bounds__(1024) void k_small_scan(int nt, const int* __restrict__ count,
                                                      int* __restrict__ coff,
                                                      int* __restrict__ soff, int cc, int cs,
-                                                     int* __restrict__ heavy_base,
+                                                     int share, int* __restrict__ heavy_base,
                                                      int4* __restrict__ heavy_unit,
                                                      int* __restrict__ heavy_count,
                                                      int* __restrict__ arrive, int slot_cap) {
@@ -3004,20 +3019,6 @@ __global__ __launch_bounds__(1024) void k_small_scan(int nt, const int* __restri
     if (t < nt) {
       if (coff) coff[t] = c0 + ic - nc;
       if (soff) soff[t] = c1 + is - ns;
-      const int chunks = tile_chunks(nc, ns, cc, cs);
-      int base = -1;
-      if (chunks > 1) {
-        const int b0 = atomicAdd(&claimed, chunks);
-        if (b0 + chunks <= slot_cap) {
-          base = b0;
-          for (int j = 0; j < chunks; ++j) heavy_unit[b0 + j] = make_int4(t, j, chunks, 0);
-          arrive[b0] = 0;
-        } else {
-          for (int j = b0; j < min(b0 + chunks, slot_cap); ++j)
-            heavy_unit[j] = make_int4(-1, 0, 0, 0);
-        }
-      }
-      heavy_base[t] = base;
     }
     __syncthreads();
     if (threadIdx.x == blockDim.x - 1) {
@@ -3026,6 +3027,23 @@ __global__ __launch_bounds__(1024) void k_small_scan(int nt, const int* __restri
     }
     __syncthreads();
   }
+  for (int t = threadIdx.x; t < nt; t += blockDim.x) {
+    const int chunks = tile_chunks(count[t], count[nt + t], cc, cs, carry[0], carry[1], share);
+    int base = -1;
+    if (chunks > 1) {
+      const int b0 = atomicAdd(&claimed, chunks);
+      if (b0 + chunks <= slot_cap) {
+        base = b0;
+        for (int j = 0; j < chunks; ++j) heavy_unit[b0 + j] = make_int4(t, j, chunks, 0);
+        arrive[b0] = 0;
+      } else {
+        for (int j = b0; j < min(b0 + chunks, slot_cap); ++j)
+          heavy_unit[j] = make_int4(-1, 0, 0, 0);
+      }
+    }
+    heavy_base[t] = base;
+  }
+  __syncthreads();
   if (threadIdx.x == 0) {
     if (coff) coff[nt] = carry[0];
     if (soff) soff[nt] = carry[1];
@@ -3074,6 +3092,21 @@ __device__ __forceinline__ void lds_add(unsigned long long* p, long long q) {
   atomicAdd(p, (unsigned long long)q);
 }
 __device__ __forceinline__ void lds_add(double* p, double v) { unsafeAtomicAdd(p, v); }
+
+// Partial sums passed between workgroups: device-scope loads and stores.
+__device__ __forceinline__ void part_store(unsigned long long* p, unsigned long long v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void part_store(double* p, double v) {
+  part_store(reinterpret_cast<unsigned long long*>(p),
+             (unsigned long long)__double_as_longlong(v));
+}
+__device__ __forceinline__ unsigned long long part_load(const unsigned long long* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ double part_load(const double* p) {
+  return __longlong_as_double((long long)part_load(reinterpret_cast<const unsigned long long*>(p)));
+}
 
 template <class T> __device__ __forceinline__ T from_lds(unsigned long long v);
 // Reproducibility mode: the addition, then the bound of the element grows by
@@ -3227,7 +3260,8 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(ACC == PMP
     // owner tiles: every contribution to the tile's cells is in its lists, so
     // with empty lists no cell changes (a tile kept for the sinks is stored)
     if (OWN && e0 == e1 && s0 == s1 && state && !(sink_flag && sink_flag[tile])) continue;
-    if (base >= 0) {
+    const bool sne = s1 > s0;  // the tile has supernovae: both channels
+    if (!BOUNDS && base >= 0) {
       // this chunk's share of the tile's entries
       const long long nc = e1 - e0, ns = s1 - s0;
       e1 = e0 + (int)(nc * (chunk + 1) / chunks);
@@ -3424,31 +3458,45 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(ACC == PMP
     }
     if (ovf) raise_flag(M.status, PMP_FLAG_OVERFLOW);
     __syncthreads();
-    if (base >= 0) {
+    if (!BOUNDS && base >= 0) {
       // a chunk of a split tile: leave the partial tile, and the last chunk
-      // to finish (device-scope fence + arrival count) sums the chunks'
-      // partial tiles in chunk order back into the accumulators
+      // to finish (arrival count) sums the chunks' partial tiles in chunk order
+      // back into the accumulators.  The partial sums are stored and loaded
+      // as device-scope atomics, past the XCD's own L2, and waited for before
+      // the arrival: a device-scope fence would write that whole L2 back, once
+      // for every chunk.
       LT* part = partial + (long long)(base + chunk) * 2 * lcells;
       for (int c = threadIdx.x; c < lcells; c += blockDim.x) {
-        part[c] = a0[c];
-        part[lcells + c] = a4[c];
+        part_store(part + c, a0[c]);
+        if (sne) part_store(part + lcells + c, a4[c]);
       }
-      __threadfence();
+      __builtin_amdgcn_s_waitcnt(0);  // this wavefront's stores have reached device scope
       __syncthreads();
-      if (threadIdx.x == 0) s_last = (atomicAdd(arrive + base, 1) == chunks - 1);
+      if (threadIdx.x == 0)
+        s_last = (__hip_atomic_fetch_add(arrive + base, 1, __ATOMIC_RELAXED,
+                                         __HIP_MEMORY_SCOPE_AGENT) == chunks - 1);
       __syncthreads();
       if (!s_last) continue;
-      __threadfence();
       const LT* p0 = partial + (long long)base * 2 * lcells;
-      for (int c = threadIdx.x; c < lcells; c += blockDim.x) {
-        LT r0 = p0[c], r4 = p0[lcells + c];
-        for (int q = 1; q < chunks; ++q) {
-          r0 += p0[2ll * q * lcells + c];
-          r4 += p0[2ll * q * lcells + lcells + c];
+      // (kCombine chunks' loads in flight, added in chunk order)
+      constexpr int kCombine = FIXED ? 4 : 8;
+      auto combine = [&](LT* acc, const LT* src) {
+        for (int c = threadIdx.x; c < lcells; c += blockDim.x) {
+          LT sum = (LT)0;
+          for (int q = 0; q < chunks; q += kCombine) {
+            LT v[kCombine];
+#pragma unroll
+            for (int j = 0; j < kCombine; ++j)
+              v[j] = q + j < chunks ? part_load(src + 2ll * (q + j) * lcells + c) : (LT)0;
+#pragma unroll
+            for (int j = 0; j < kCombine; ++j)
+              if (q + j < chunks) sum = (q + j == 0) ? v[j] : sum + v[j];
+          }
+          acc[c] = sum;
         }
-        a0[c] = r0;
-        a4[c] = r4;
-      }
+      };
+      combine(a0, p0);
+      if (sne) combine(a4, p0 + lcells);
       __syncthreads();
     }
     // every present channel of every cell is stored once: rho and E from
@@ -3707,12 +3755,18 @@ hipError_t launch_cic_direct(const Mesh& M, const Particles& P, void* buf, int b
 }
 
 
+// Workgroups a deposit's entries are shared over before tiles are split (see
+// tile_chunks); 0 in the reproducibility mode, which never splits a tile: each
+// tile sums all of its cells' contributions (and their bounds).
+static int chunk_share(const Mesh& M) { return M.acc == PMP_ACC_F64R ? 0 : 2 * M.num_cu; }
+
 // Chunk slots a deposit can need: a tile is split only past a chunk's length,
 // so its chunks number at most twice its entries over that length.
 static int chunk_slots(const Particles* cic, const Particles* sn, const BinWork& bw,
                        const pmp_tuning& t) {
-  const double c = cic && cic->n > 0 ? 16.0 * (double)cic->n / t.chunk_cic : 0.0;
-  const double q = sn && sn->n > 0 ? 2.0 * bw.sn_slots * (double)sn->n / t.chunk_sn : 0.0;
+  const double lc = std::min(t.chunk_cic, kChunkMinCic), ls = std::min(t.chunk_sn, kChunkMinSn);
+  const double c = cic && cic->n > 0 ? 16.0 * (double)cic->n / lc : 0.0;
+  const double q = sn && sn->n > 0 ? 2.0 * bw.sn_slots * (double)sn->n / ls : 0.0;
   return (int)std::min((double)bw.slot_cap, floor(c + q));
 }
 
@@ -3724,10 +3778,7 @@ static hipError_t launch_tile_prep(const Mesh& M, const TileGrid& T, const Parti
   const int* soff = (sn && sn->n > 0) ? bw.sn_off : nullptr;
   hipLaunchKernelGGL(k_units, dim3(grid_for(T.ntiles, 256, M.num_cu * 16)), dim3(256), 0, s, T,
                      coff, soff,
-                     // the reproducibility mode never splits a tile: each tile
-                     // sums all of its cells' contributions (and their bounds)
-                     M.acc == PMP_ACC_F64R ? 0x7fffffff : t.chunk_cic,
-                     M.acc == PMP_ACC_F64R ? 0x7fffffff : t.chunk_sn, bw.heavy_base,
+                     t.chunk_cic, t.chunk_sn, chunk_share(M), bw.heavy_base,
                      bw.heavy_unit, bw.heavy_count, bw.arrive, chunk_slots(cic, sn, bw, t));
   return hipGetLastError();
 }
@@ -3752,12 +3803,11 @@ static hipError_t launch_bin_small(const Mesh& M, const TileGrid& T, const Parti
   else if (M.own_start == nullptr) PMP_SMALL(2);  // one box covers the domain
   else PMP_SMALL(1);
 #undef PMP_SMALL
-  const bool repro = M.acc == PMP_ACC_F64R;  // never splits a tile (see launch_tile_prep)
   int* coff = has_c ? bw.cic_off : nullptr;
   int* soff = has_s ? bw.sn_off : nullptr;
   hipLaunchKernelGGL(k_small_scan, dim3(1), dim3(1024), 0, s, nt, (const int*)count, coff, soff,
-                     repro ? 0x7fffffff : t.chunk_cic, repro ? 0x7fffffff : t.chunk_sn,
-                     bw.heavy_base, bw.heavy_unit, bw.heavy_count, bw.arrive,
+                     t.chunk_cic, t.chunk_sn, chunk_share(M), bw.heavy_base,
+                     bw.heavy_unit, bw.heavy_count, bw.arrive,
                      chunk_slots(cic, sn, bw, t));
   const int nfs = has_s ? (int)((sn->n + 255) / 256) : 0;
   hipLaunchKernelGGL(k_small_fill, dim3(nbc + nfs), dim3(256), 0, s, has_c ? cic->n : 0,
@@ -3889,7 +3939,7 @@ hipError_t launch_tile_deposit(const Mesh& M, const TileGrid& T, const Particles
   const int* soff = (sn && sn->n > 0) ? bw.sn_off : nullptr;
   const int block = t.tile_block;
   const size_t lds = (size_t)tile_lds_bytes_wx(T.wx, T.t[1], M.acc == PMP_ACC_F64R);
-  const int slots = chunk_slots(cic, sn, bw, t);
+  const int slots = M.acc == PMP_ACC_F64R ? 0 : chunk_slots(cic, sn, bw, t);
   long long grid = T.ntiles + slots;
   if (t.tile_grid_per_cu > 0)
     grid = std::min<long long>(grid, (long long)M.num_cu * t.tile_grid_per_cu);
