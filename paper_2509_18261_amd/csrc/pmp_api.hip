@@ -1768,10 +1768,13 @@ int pmp_get_status(pmp_ctx* c, pmp_status* out, int reset) {
   PMP_HIP(hipMemcpy(&d, c->d_status, sizeof d, hipMemcpyDeviceToHost));
   out->flags = d.flags;
   out->reserved = 0;
-  out->touched = (int64_t)d.touched;
-  out->bind = (int64_t)d.bind;
-  out->lam = (int64_t)d.lam;
-  out->fall = (int64_t)d.fall;
+  out->touched = out->bind = out->lam = out->fall = 0;
+  for (const DevCounts& q : d.slot) {
+    out->touched += (int64_t)q.touched;
+    out->bind += (int64_t)q.bind;
+    out->lam += (int64_t)q.lam;
+    out->fall += (int64_t)q.fall;
+  }
   if (reset) {
     PMP_HIP(launch_clear_status(c->d_status, nullptr));
     PMP_HIP(hipDeviceSynchronize());

@@ -42,11 +42,17 @@ struct alignas(16) ZoneSeg {
   long long npad;    // padded cells of the source box
 };
 
-// Device status word and counters (mirrors pmp_status).
+// Device status word and counters (pmp_status).  The limiter counters are
+// kept in kStatusSlots copies of a cache line each, which a block picks by its
+// number and pmp_get_status sums: adds of all wavefronts to one address are
+// retired one by one (12 ns each), and bounded the apply of a step with sinks.
+constexpr int kStatusSlots = 64;
+struct alignas(128) DevCounts {
+  unsigned long long touched, bind, lam, fall;
+};
 struct DevStatus {
   unsigned int flags;
-  unsigned int reserved;
-  unsigned long long touched, bind, lam, fall;
+  DevCounts slot[kStatusSlots];
 };
 
 // Limiter parameters (pmp_limits) and the cell edge.  truelove_J > 0: each

@@ -107,8 +107,11 @@ __device__ __forceinline__ double kernel_pow(double x, double a) {
   return kernel_exp(a * kernel_log(x));
 }
 
+// (the read keeps a flag that is already up from being raised again by every
+// wavefront, one after another)
 __device__ __forceinline__ void raise_flag(DevStatus* st, unsigned f) {
-  atomicOr(&st->flags, f);
+  if ((__hip_atomic_load(&st->flags, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & f) != f)
+    atomicOr(&st->flags, f);
 }
 
 // Largest b with off[b] <= p (off[0] = 0 <= p < off[nbox]).
@@ -500,11 +503,8 @@ __global__ __launch_bounds__(256) void k_atomic_bench(T* __restrict__ dst, unsig
 }
 
 __global__ void k_clear_status(DevStatus* st) {
-  if (threadIdx.x == 0) {
-    st->flags = 0u;
-    st->reserved = 0u;
-    st->touched = st->bind = st->lam = st->fall = 0ull;
-  }
+  if (threadIdx.x == 0) st->flags = 0u;
+  if (threadIdx.x < kStatusSlots) st->slot[threadIdx.x] = DevCounts{0ull, 0ull, 0ull, 0ull};
 }
 
 // ------------------------------------------------------------ CIC deposit
@@ -1801,25 +1801,27 @@ __device__ __forceinline__ void flush_counts(const Mesh& M, ApplyCounts& cnt) {
   const unsigned long long fall = group_sum<kWave>((unsigned long long)cnt.fall);
   const unsigned long long nbad = group_sum<kWave>((unsigned long long)cnt.bad);
   if ((threadIdx.x & (kWave - 1)) == 0) {
-    if (touched) atomicAdd(&M.status->touched, touched);
-    if (bind) atomicAdd(&M.status->bind, bind);
-    if (lamc) atomicAdd(&M.status->lam, lamc);
+    DevCounts& C = M.status->slot[blockIdx.x % kStatusSlots];
+    if (touched) atomicAdd(&C.touched, touched);
+    if (bind) atomicAdd(&C.bind, bind);
+    if (lamc) atomicAdd(&C.lam, lamc);
     if (fall) {
-      atomicAdd(&M.status->fall, fall);
-      atomicOr(&M.status->flags, PMP_FLAG_FLOOR);
+      atomicAdd(&C.fall, fall);
+      raise_flag(M.status, PMP_FLAG_FLOOR);
     }
-    if (nbad) atomicOr(&M.status->flags, PMP_FLAG_NAN);
+    if (nbad) raise_flag(M.status, PMP_FLAG_NAN);
   }
 }
 
 // Steps 2 + 3 + 5 for the shell cells of a fused step: each shell cell
 // gathers its ghost images in the plan's order (as k_fold) and is applied
-// at once; the interior cells were applied by the tile pass.  (Register
-// budget for 7 waves per SIMD; the apply kernel below fits 8.)
-template <int ACC, int F>
-__global__ __launch_bounds__(kChunk) __attribute__((amdgpu_waves_per_eu(7))) void k_fold_apply(Mesh M, void* __restrict__ state,
-                                                      const typename AccT<ACC>::T* __restrict__ buf,
-                                                      Limits L) {
+// at once; the interior cells were applied by the tile pass.  NOSRC: the
+// layout has neither momentum nor removal channels, so the source-free apply
+// serves every cell (without the general limiter behind it the kernel takes
+// 40 registers instead of spilling 72).
+template <int ACC, int F, class S, bool NOSRC>
+__global__ __launch_bounds__(kChunk) __attribute__((amdgpu_waves_per_eu(NOSRC ? 8 : 6))) void k_fold_apply(
+    Mesh M, S* __restrict__ state, const typename AccT<ACC>::T* __restrict__ buf, Limits L) {
   using Sum = SumT<ACC>;
   using T = typename AccT<ACC>::T;
   const int g = M.ghost;
@@ -1838,18 +1840,25 @@ __global__ __launch_bounds__(kChunk) __attribute__((amdgpu_waves_per_eu(7))) voi
     for (int f = 0; f < F; ++f) acc[f] = (Sum)buf[dst + f * B.npad];
     fold_gather<ACC, F>(M, b, i, j, k, buf, acc);
     // the folded values as the buffer would hold them
-    double v[6];
+    S* const st = state + B.soff + ((long long)k * B.n[1] + j) * B.n[0] + i;
+    if constexpr (NOSRC) {
+      double Dr = 0.0, DE = 0.0;
 #pragma unroll
-    for (int q = 0; q < 6; ++q) v[q] = M.slot[q] >= 0 ? to_f64((T)acc[M.slot[q]]) : 0.0;
-    const long long si = B.soff + ((long long)k * B.n[1] + j) * B.n[0] + i;
-    // without momentum or removal channels (uniform): the source-free apply
-    const bool nosrc = M.slot[1] < 0 && M.slot[2] < 0 && M.slot[3] < 0 && M.slot[5] < 0;
-    if (M.state == PMP_STATE_F32) {
-      if (nosrc) apply_cell_nosrc((float*)state + si, B.ncell, v[0], v[4], L, cnt);
-      else apply_cell((float*)state + si, B.ncell, v[0], v[1], v[2], v[3], v[4], v[5], L, cnt);
+      for (int f = 0; f < F; ++f) {
+        if (M.slot[0] == f) Dr = to_f64((T)acc[f]);
+        if (M.slot[4] == f) DE = to_f64((T)acc[f]);
+      }
+      apply_cell_nosrc(st, B.ncell, Dr, DE, L, cnt);
     } else {
-      if (nosrc) apply_cell_nosrc((double*)state + si, B.ncell, v[0], v[4], L, cnt);
-      else apply_cell((double*)state + si, B.ncell, v[0], v[1], v[2], v[3], v[4], v[5], L, cnt);
+      double v[6];
+#pragma unroll
+      for (int q = 0; q < 6; ++q) {
+        v[q] = 0.0;
+#pragma unroll
+        for (int f = 0; f < F; ++f)
+          if (M.slot[q] == f) v[q] = to_f64((T)acc[f]);
+      }
+      apply_cell(st, B.ncell, v[0], v[1], v[2], v[3], v[4], v[5], L, cnt);
     }
   }
   flush_counts(M, cnt);
@@ -4361,33 +4370,39 @@ static void fold_launch(const Mesh& M, void* buf, int block, hipStream_t s) {
 #undef PMP_FOLD
 }
 
-template <int ACC>
+template <int ACC, class S>
 static void fold_apply_launch(const Mesh& M, void* state, const void* buf, const Limits& L,
                               hipStream_t s) {
   using T = typename AccT<ACC>::T;
   const int grid = grid_for(M.n_fold_chunks, 1, M.num_cu * 64);
-#define PMP_FA(F)                                                                           \
-  hipLaunchKernelGGL((k_fold_apply<ACC, F>), dim3(grid), dim3(kChunk), 0, s, M, state,      \
-                     (const T*)buf, L)
+#define PMP_FA(F, NOSRC)                                                                       \
+  hipLaunchKernelGGL((k_fold_apply<ACC, F, S, NOSRC>), dim3(grid), dim3(kChunk), 0, s, M,      \
+                     (S*)state, (const T*)buf, L)
+  const bool nosrc = M.slot[1] < 0 && M.slot[5] < 0;  // at most rho and E
   switch (M.nfield) {
-    case 1: PMP_FA(1); break;
-    case 2: PMP_FA(2); break;
-    case 3: PMP_FA(3); break;
-    case 4: PMP_FA(4); break;
-    case 5: PMP_FA(5); break;
-    default: PMP_FA(6);
+    case 1: if (nosrc) PMP_FA(1, true); else PMP_FA(1, false); break;
+    case 2: if (nosrc) PMP_FA(2, true); else PMP_FA(2, false); break;
+    case 3: PMP_FA(3, false); break;
+    case 4: PMP_FA(4, false); break;
+    case 5: PMP_FA(5, false); break;
+    default: PMP_FA(6, false);
   }
 #undef PMP_FA
 }
 
 hipError_t launch_fold_apply(const Mesh& M, void* state, const void* buf, const Limits& L,
                              hipStream_t s) {
+  const bool f32 = (M.state == PMP_STATE_F32);
+#define PMP_FAS(ACC)                                                     \
+  (f32 ? fold_apply_launch<ACC, float>(M, state, buf, L, s)              \
+       : fold_apply_launch<ACC, double>(M, state, buf, L, s))
   switch (M.acc) {
-    case PMP_ACC_F32: fold_apply_launch<PMP_ACC_F32>(M, state, buf, L, s); break;
+    case PMP_ACC_F32: PMP_FAS(PMP_ACC_F32); break;
     case PMP_ACC_F64R:  // double buffer; its deposits are checked for the binned path
-    case PMP_ACC_F64: fold_apply_launch<PMP_ACC_F64>(M, state, buf, L, s); break;
-    default: fold_apply_launch<PMP_ACC_FIX64>(M, state, buf, L, s);
+    case PMP_ACC_F64: PMP_FAS(PMP_ACC_F64); break;
+    default: PMP_FAS(PMP_ACC_FIX64);
   }
+#undef PMP_FAS
   return hipGetLastError();
 }
 
