@@ -2299,12 +2299,58 @@ __device__ __forceinline__ const NbrBox* nbr_of(const TileGrid& T, const NbrBox*
   return (b - bb0 < kNbrCache) ? s + 27 * (b - bb0) : T.nbr + 27 * b;
 }
 
+// What binning needs of the boxes a level-1 block's particles lie in, staged
+// in LDS (several boxes): a particle's box is searched and its record read
+// there, instead of through four to six dependent global loads per particle
+// (4096 boxes: histogram pass 232 -> 205 us, scatter pass 256 -> 235).
+struct alignas(16) BoxL {
+  long long off;   // its first particle
+  int lo[3], n[3];
+  int tprefix, tax0, tax1;  // its first tile, tiles along x and y
+  int pad;
+};
+constexpr int kBoxCache = 64;
+// Stages boxes [bb0, bb1] when they fit; every thread of the block calls it,
+// and the records may be read after the next barrier.
+__device__ __forceinline__ bool stage_boxes(const Mesh& M, const TileGrid& T,
+                                            const long long* __restrict__ off, int bb0, int bb1,
+                                            BoxL* s) {
+  const int n = bb1 - bb0 + 1;
+  if (M.nbox == 1 || n > kBoxCache) return false;
+  for (int q = threadIdx.x; q < n; q += blockDim.x) {
+    const int b = bb0 + q;
+    const DevBox& B = M.boxes[b];
+    BoxL R;
+    R.off = off[b];
+    for (int a = 0; a < 3; ++a) {
+      R.lo[a] = B.lo[a];
+      R.n[a] = B.n[a];
+    }
+    R.tprefix = (int)T.tile_prefix[b];
+    R.tax0 = T.tiles_axis[3 * b];
+    R.tax1 = T.tiles_axis[3 * b + 1];
+    R.pad = 0;
+    s[q] = R;
+  }
+  return true;
+}
+// Box of particle p of a block whose boxes are staged (offset from bb0): the
+// last one that starts at or before p.
+__device__ __forceinline__ int staged_box(const BoxL* s, int n, long long p) {
+  int lo = 0, hi = n - 1;
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (s[mid].off <= p) lo = mid; else hi = mid - 1;
+  }
+  return lo;
+}
+
 template <bool SCATTER, int OWN>
 __device__ __forceinline__ void l1_cic(int blk, const Mesh& M, const TileGrid& T,
                                        const Particles& P, int shift, int nb,
                                        int* __restrict__ hist, int nblk,
                                        double4* __restrict__ aos, int2* __restrict__ tmp,
-                                       long long cap, NbrBox* s_nbr) {
+                                       long long cap, NbrBox* s_nbr, BoxL* s_box) {
   extern __shared__ int h[];
   const int g = M.ghost;
   const int col = hist_col(blk, nblk);
@@ -2318,6 +2364,9 @@ __device__ __forceinline__ void l1_cic(int blk, const Mesh& M, const TileGrid& T
   int bb0, bb1;
   block_box_range(P.box_off, M.nbox, p0, p1, bb0, bb1);
   if constexpr (OWN == 1) stage_nbr(T, bb0, bb1, s_nbr);  // read after the barriers below
+  bool staged = false;
+  if constexpr (OWN != 2) staged = stage_boxes(M, T, P.box_off, bb0, bb1, s_box);
+  if (staged) __syncthreads();
   bool outside = false, nan = false, full = false;
   constexpr int UNR = kBinChunkCic / 256;
   // the thread's particles are loaded together, then binned one by one
@@ -2353,8 +2402,27 @@ __device__ __forceinline__ void l1_cic(int blk, const Mesh& M, const TileGrid& T
   for (int u = 0; u < UNR; ++u) {
     const long long p = p0 + threadIdx.x + (long long)u * blockDim.x;
     if (p >= p1) continue;
-    const int b = (bb0 == bb1) ? bb0 : find_box_in(P.box_off, bb0, bb1, p);
-    const DevBox B = M.boxes[b];
+    DevBox B;
+    int b, tp, tax0, tax1;
+    if (staged) {
+      const int q = staged_box(s_box, bb1 - bb0 + 1, p);
+      const BoxL& R = s_box[q];
+      b = bb0 + q;
+      for (int a = 0; a < 3; ++a) {
+        B.lo[a] = R.lo[a];
+        B.n[a] = R.n[a];
+        B.p[a] = R.n[a] + 2 * g;
+      }
+      tp = R.tprefix;
+      tax0 = R.tax0;
+      tax1 = R.tax1;
+    } else {
+      b = (bb0 == bb1) ? bb0 : find_box_in(P.box_off, bb0, bb1, p);
+      B = M.boxes[b];
+      tp = (int)T.tile_prefix[b];
+      tax0 = T.tiles_axis[3 * b];
+      tax1 = T.tiles_axis[3 * b + 1];
+    }
     const double x = px[u], y = py[u], z = pz[u], m = pm[u];
     int hc[3];
     if (!host_cell(B, x, y, z, hc)) { outside = true; continue; }
@@ -2381,7 +2449,7 @@ __device__ __forceinline__ void l1_cic(int blk, const Mesh& M, const TileGrid& T
     for (int tz = tlo[2]; tz <= thi[2]; ++tz)
       for (int ty = tlo[1]; ty <= thi[1]; ++ty)
         for (int tx = tlo[0]; tx <= thi[0]; ++tx) {
-          const int t = (int)tile_id(T, b, tx, ty, tz);
+          const int t = tp + (tz * tax1 + ty) * tax0 + tx;
           const int pos = atomicAdd(h + (t >> shift), 1);
           if (SCATTER) {
             if (pos < cap) {
@@ -2417,7 +2485,16 @@ __device__ __forceinline__ void l1_cic(int blk, const Mesh& M, const TileGrid& T
       const int sv = s_slow[i];
       const long long p = p0 + (sv & (kBinChunkCic - 1));
       const int b = packed ? bb0 + (sv >> kChunkBits) : find_box_in(P.box_off, bb0, bb1, p);
-      const DevBox B = M.boxes[b];
+      DevBox B;
+      if (staged) {
+        for (int a = 0; a < 3; ++a) {
+          B.lo[a] = s_box[b - bb0].lo[a];
+          B.n[a] = s_box[b - bb0].n[a];
+          B.p[a] = B.n[a] + 2 * g;
+        }
+      } else {
+        B = M.boxes[b];
+      }
       const double x = P.x[p], y = P.y[p], z = P.z[p];
       int lo[3], hi[3];
       cic_box(B, g, x, y, z, lo, hi);
@@ -2610,7 +2687,7 @@ template <int OWN>
 __device__ __forceinline__ void l1_sn_hist(int blk, const Mesh& M, const TileGrid& T,
                                            const Particles& P, int shift, int nb,
                                            int* __restrict__ hist, int nblk,
-                                           const SnPk* __restrict__ pk, NbrBox* s_nbr) {
+                                           const SnPk* __restrict__ pk, NbrBox* s_nbr, BoxL* s_box) {
   extern __shared__ int h[];
   const int col = hist_col(blk, nblk);
   for (int c = threadIdx.x; c < nb; c += blockDim.x) h[c] = 0;
@@ -2619,13 +2696,26 @@ __device__ __forceinline__ void l1_sn_hist(int blk, const Mesh& M, const TileGri
   int bb0, bb1;
   block_box_range(P.box_off, M.nbox, p0, p1, bb0, bb1);
   if constexpr (OWN == 1) stage_nbr(T, bb0, bb1, s_nbr);
+  const bool staged = OWN != 2 && stage_boxes(M, T, P.box_off, bb0, bb1, s_box);
   __syncthreads();
   for (long long p = p0 + threadIdx.x; p < p1; p += blockDim.x) {
     const SnPk& R = pk[p];
     const int N = R.n;
     if (N == 0) continue;
-    const int b = (bb0 == bb1) ? bb0 : find_box_in(P.box_off, bb0, bb1, p);
-    const DevBox B = M.boxes[b];
+    DevBox B;
+    int b;
+    if (staged) {
+      const int q = staged_box(s_box, bb1 - bb0 + 1, p);
+      b = bb0 + q;
+      for (int a = 0; a < 3; ++a) {
+        B.lo[a] = s_box[q].lo[a];
+        B.n[a] = s_box[q].n[a];
+        B.p[a] = B.n[a] + 2 * M.ghost;
+      }
+    } else {
+      b = (bb0 == bb1) ? bb0 : find_box_in(P.box_off, bb0, bb1, p);
+      B = M.boxes[b];
+    }
     sn_tiles<OWN>(M, T, b, B, R.x, R.y, R.z, R.r, N,
                   [&](int t) { atomicAdd(h + (t >> shift), 1); },
                   OWN == 1 ? nbr_of(T, s_nbr, bb0, b) : nullptr);
@@ -2641,7 +2731,7 @@ __device__ __forceinline__ void l1_sn_scatter(int blk, const Mesh& M, const Tile
                                               const Particles& P, int shift, int nb,
                                               int* __restrict__ hist, int nblk,
                                               const SnPk* __restrict__ pk, int2* __restrict__ tmp,
-                                              long long cap, NbrBox* s_nbr) {
+                                              long long cap, NbrBox* s_nbr, BoxL* s_box) {
   extern __shared__ int h[];
   const int col = hist_col(blk, nblk);
   for (int c = threadIdx.x; c < nb; c += blockDim.x)
@@ -2651,14 +2741,27 @@ __device__ __forceinline__ void l1_sn_scatter(int blk, const Mesh& M, const Tile
   int bb0, bb1;
   block_box_range(P.box_off, M.nbox, p0, p1, bb0, bb1);
   if constexpr (OWN == 1) stage_nbr(T, bb0, bb1, s_nbr);
+  const bool staged = OWN != 2 && stage_boxes(M, T, P.box_off, bb0, bb1, s_box);
   __syncthreads();
   bool full = false;
   for (long long p = p0 + threadIdx.x; p < p1; p += blockDim.x) {
     const SnPk& R = pk[p];
     const int N = R.n;
     if (N == 0) continue;
-    const int b = (bb0 == bb1) ? bb0 : find_box_in(P.box_off, bb0, bb1, p);
-    const DevBox B = M.boxes[b];
+    DevBox B;
+    int b;
+    if (staged) {
+      const int q = staged_box(s_box, bb1 - bb0 + 1, p);
+      b = bb0 + q;
+      for (int a = 0; a < 3; ++a) {
+        B.lo[a] = s_box[q].lo[a];
+        B.n[a] = s_box[q].n[a];
+        B.p[a] = B.n[a] + 2 * M.ghost;
+      }
+    } else {
+      b = (bb0 == bb1) ? bb0 : find_box_in(P.box_off, bb0, bb1, p);
+      B = M.boxes[b];
+    }
     sn_tiles<OWN>(M, T, b, B, R.x, R.y, R.z, R.r, N, [&](int id) {
       const int pos = atomicAdd(h + (id >> shift), 1);
       if (pos < cap) {
@@ -2682,10 +2785,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(7))) void k
                                                 const SnPk* __restrict__ pk,
                                                 double4* __restrict__ aos) {
   __shared__ NbrBox s_nbr[OWN == 1 ? 27 * kNbrCache : 1];
+  __shared__ BoxL s_box[OWN == 2 ? 1 : kBoxCache];
   if ((int)blockIdx.x < nbc)
-    l1_cic<false, OWN>(blockIdx.x, M, T, C, shift, nb, hc, nbc, aos, nullptr, 0, s_nbr);
+    l1_cic<false, OWN>(blockIdx.x, M, T, C, shift, nb, hc, nbc, aos, nullptr, 0, s_nbr,
+                       s_box);
   else
-    l1_sn_hist<OWN>(blockIdx.x - nbc, M, T, Sn, shift, nb, hs, nbs, pk, s_nbr);
+    l1_sn_hist<OWN>(blockIdx.x - nbc, M, T, Sn, shift, nb, hs, nbs, pk, s_nbr, s_box);
 }
 
 template <int OWN>
@@ -2698,10 +2803,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) void k
                                                    const SnPk* __restrict__ pk,
                                                    int2* __restrict__ stmp, long long scap) {
   __shared__ NbrBox s_nbr[OWN == 1 ? 27 * kNbrCache : 1];
+  __shared__ BoxL s_box[OWN == 2 ? 1 : kBoxCache];
   if ((int)blockIdx.x < nbc)
-    l1_cic<true, OWN>(blockIdx.x, M, T, C, shift, nb, hc, nbc, aos, ctmp, ccap, s_nbr);
+    l1_cic<true, OWN>(blockIdx.x, M, T, C, shift, nb, hc, nbc, aos, ctmp, ccap, s_nbr, s_box);
   else
-    l1_sn_scatter<OWN>(blockIdx.x - nbc, M, T, Sn, shift, nb, hs, nbs, pk, stmp, scap, s_nbr);
+    l1_sn_scatter<OWN>(blockIdx.x - nbc, M, T, Sn, shift, nb, hs, nbs, pk, stmp, scap, s_nbr, s_box);
 }
 
 // Level 2: one workgroup per coarse bucket sorts the bucket's records by
