@@ -3935,7 +3935,10 @@ hipError_t launch_bin(const Mesh& M, const TileGrid& T, const Particles* cic,
                       const Particles* sn, BinWork& bw, const pmp_tuning& t, hipStream_t s) {
   const int nb = bw.nbuckets, S = bw.shift, count_lanes = t.count_lanes;
   const bool has_c = cic && cic->n > 0, has_s = sn && sn->n > 0;
-  if (T.ntiles <= kSmallTiles &&
+  // (not in the reproducibility mode: its truncation follows the order of the
+  // additions, and the short sort's order of entries varies from run to run
+  // where the two-level sort's mostly does not)
+  if (M.acc != PMP_ACC_F64R && T.ntiles <= kSmallTiles &&
       (has_c ? cic->n : 0) + 8 * (has_s ? sn->n : 0) <= kSmallEntries)
     return launch_bin_small(M, T, cic, sn, bw, t, s);
   const int nbc = has_c ? (int)((cic->n + kBinChunkCic - 1) / kBinChunkCic) : 0;
