@@ -2954,8 +2954,8 @@ __global__ __launch_bounds__(256) void k_l2_scatter(L2Geom G, const int* __restr
       if (q == 0 && f < nf) off[t0 + f] = v;
     }
     __syncthreads();
-    // eight entries per thread in flight: loaded together, then ranked and stored
-    constexpr int U = 8;
+    // four entries per thread in flight: loaded together, then ranked and stored
+    constexpr int U = 4;
     const long long stride = blockDim.x;
     for (long long e = e0 + threadIdx.x; e < e1; e += U * stride) {
       int2 v[U];
