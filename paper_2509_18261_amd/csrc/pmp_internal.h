@@ -45,7 +45,8 @@ struct alignas(16) ZoneSeg {
 // Device status word and counters (pmp_status).  The limiter counters are
 // kept in kStatusSlots copies of a cache line each, which a block picks by its
 // number and pmp_get_status sums: adds of all wavefronts to one address are
-// retired one by one (12 ns each), and bounded the apply of a step with sinks.
+// retired one by one (12 ns each), and bounded the apply of a step with sinks
+// (256^3, 256 sinks: 33 us with one copy, 19 with these).
 constexpr int kStatusSlots = 64;
 struct alignas(128) DevCounts {
   unsigned long long touched, bind, lam, fall;
@@ -196,9 +197,10 @@ struct alignas(16) SnTile {
 
 // Scratch for the binned deposit, owned by the context.  (particle, tile)
 // pairs are bucket-sorted in two levels with LDS-only ranking: level 1 moves
-// each pair's record into its coarse bucket (tile >> shift) through per-block
+// each pair into its coarse bucket (tile >> shift) through per-block
 // histograms and a global scan; level 2 sorts each bucket by tile and writes
-// the per-tile offsets.
+// the per-tile offsets.  A small deposit's sort uses the same arrays in three
+// kernels (counts per tile in hist2, pair slots in cic_tmp and sn_tmp).
 struct BinWork {
   int shift;            // coarse bucket = tile >> shift
   int nbuckets;         // ceil(ntiles / 2^shift) <= 1024
@@ -263,11 +265,10 @@ constexpr int kBinChunkSn = 256;    // supernovae per level-1 block (one per thr
 hipError_t launch_zero(void* buf, long long bytes, int block, hipStream_t s);
 hipError_t launch_cic_direct(const Mesh& M, const Particles& P, void* buf, int block,
                              hipStream_t s);
-// Binned path: bin CIC and supernova particles into tiles, then one
-// workgroup per tile accumulates in LDS and stores every field of its cells.
-// cic or sn may be null.  Replaces the zero fill.  phase_bin/phase_tile
-// bracket the two halves for the profiler.
-// (the sort, and the chunk table of split tiles)
+// Binned path: bin CIC and supernova particles into tiles (the sort, and the
+// chunk table of split tiles), then one workgroup per tile accumulates in LDS
+// and stores every field of its cells.  cic or sn may be null.  Replaces the
+// zero fill.
 hipError_t launch_bin(const Mesh& M, const TileGrid& T, const Particles* cic,
                       const Particles* sn, BinWork& bw, const pmp_tuning& t, hipStream_t s);
 // state non-null: the step's Steps 3 + 5 are fused in for owned cells at
