@@ -2281,8 +2281,8 @@ __global__ __launch_bounds__(kScanBlock) void k_scan_finish(int* __restrict__ of
 // Bound by the latency of its scattered stores: a pair is 8 bytes and the
 // particle is stored once, in its own order, so the two levels move 8 bytes
 // per pair where they moved the particle (36): at 512^3 with 4e6 particles
-// level 1 takes 70 + 73 us (histogram + scatter; 55 + 168 before) and the
-// level-2 scatter 37 us (153 before); the tile pass then gathers the records
+// the level-1 scatter takes 73 us (168 before; the histogram pass, which
+// writes the records, 70 instead of 55) and the level-2 scatter 37 us (153); the tile pass then gathers the records
 // through the sorted indices at its old time.
 // Column of level-1 block blk in a bucket's row of the histogram: blocks
 // grouped by XCD (block i runs on XCD i mod 8), so that the counts sharing a
@@ -2677,24 +2677,28 @@ __device__ __forceinline__ int sn_members(int blk, const Mesh& M, const Particle
   return R.n;
 }
 
-template <int L>
-__global__ __launch_bounds__(256) void k_sn_count(Mesh M, Particles P, SnPk* __restrict__ pk,
-                                                  int wrap) {
-  int b;
-  DevBox B;
-  long long p;
-  SnPk R;
-  sn_members<L>(blockIdx.x, M, P, pk, wrap, b, B, p, R);
+// What binning needs of supernova (x, y, z, r) in box B before its members
+// are counted: 0 when it is skipped, 1 when a cell centre lies within r, -1
+// when none does (the host cell takes the deposit).  The host cell's centre is
+// the nearest along every axis, and the rounded squares and sums of the
+// membership test are monotone, so it is a member when any cell is.  A
+// supernova skipped for its masses has entries all the same; with n = 0 in its
+// SnPk the tile pass adds nothing for them.
+__device__ __forceinline__ int sn_bin_kind(const Mesh& M, const DevBox& B, double x, double y,
+                                           double z, double r) {
+  int hc[3];
+  if (!host_cell(B, x, y, z, hc) || !(r >= 0.0) || !(floor(r + 0.5) <= (double)M.ghost)) return 0;
+  return dist2(x, y, z, hc[0], hc[1], hc[2]) <= r * r ? 1 : -1;
 }
 
 // Level 1, supernovae, histogram pass: one thread per particle counts it
 // into the buckets of every tile its sphere touches (kBinChunkSn particles
-// per block; skipped particles have n = 0).
+// per block).
 template <int OWN>
 __device__ __forceinline__ void l1_sn_hist(int blk, const Mesh& M, const TileGrid& T,
                                            const Particles& P, int shift, int nb,
-                                           int* __restrict__ hist, int nblk,
-                                           const SnPk* __restrict__ pk, NbrBox* s_nbr, BoxL* s_box) {
+                                           int* __restrict__ hist, int nblk, NbrBox* s_nbr,
+                                           BoxL* s_box) {
   extern __shared__ int h[];
   const int col = hist_col(blk, nblk);
   for (int c = threadIdx.x; c < nb; c += blockDim.x) h[c] = 0;
@@ -2706,9 +2710,7 @@ __device__ __forceinline__ void l1_sn_hist(int blk, const Mesh& M, const TileGri
   const bool staged = OWN != 2 && stage_boxes(M, T, P.box_off, bb0, bb1, s_box);
   __syncthreads();
   for (long long p = p0 + threadIdx.x; p < p1; p += blockDim.x) {
-    const SnPk& R = pk[p];
-    const int N = R.n;
-    if (N == 0) continue;
+    const double x = P.x[p], y = P.y[p], z = P.z[p], r = P.r[p];
     DevBox B;
     int b;
     if (staged) {
@@ -2723,7 +2725,9 @@ __device__ __forceinline__ void l1_sn_hist(int blk, const Mesh& M, const TileGri
       b = (bb0 == bb1) ? bb0 : find_box_in(P.box_off, bb0, bb1, p);
       B = M.boxes[b];
     }
-    sn_tiles<OWN>(M, T, b, B, R.x, R.y, R.z, R.r, N,
+    const int N = sn_bin_kind(M, B, x, y, z, r);
+    if (N == 0) continue;
+    sn_tiles<OWN>(M, T, b, B, x, y, z, r, N,
                   [&](int t) { atomicAdd(h + (t >> shift), 1); },
                   OWN == 1 ? nbr_of(T, s_nbr, bb0, b) : nullptr);
   }
@@ -2737,7 +2741,7 @@ template <int OWN>
 __device__ __forceinline__ void l1_sn_scatter(int blk, const Mesh& M, const TileGrid& T,
                                               const Particles& P, int shift, int nb,
                                               int* __restrict__ hist, int nblk,
-                                              const SnPk* __restrict__ pk, int2* __restrict__ tmp,
+                                              int2* __restrict__ tmp,
                                               long long cap, NbrBox* s_nbr, BoxL* s_box) {
   extern __shared__ int h[];
   const int col = hist_col(blk, nblk);
@@ -2752,9 +2756,7 @@ __device__ __forceinline__ void l1_sn_scatter(int blk, const Mesh& M, const Tile
   __syncthreads();
   bool full = false;
   for (long long p = p0 + threadIdx.x; p < p1; p += blockDim.x) {
-    const SnPk& R = pk[p];
-    const int N = R.n;
-    if (N == 0) continue;
+    const double x = P.x[p], y = P.y[p], z = P.z[p], r = P.r[p];
     DevBox B;
     int b;
     if (staged) {
@@ -2769,7 +2771,9 @@ __device__ __forceinline__ void l1_sn_scatter(int blk, const Mesh& M, const Tile
       b = (bb0 == bb1) ? bb0 : find_box_in(P.box_off, bb0, bb1, p);
       B = M.boxes[b];
     }
-    sn_tiles<OWN>(M, T, b, B, R.x, R.y, R.z, R.r, N, [&](int id) {
+    const int N = sn_bin_kind(M, B, x, y, z, r);
+    if (N == 0) continue;
+    sn_tiles<OWN>(M, T, b, B, x, y, z, r, N, [&](int id) {
       const int pos = atomicAdd(h + (id >> shift), 1);
       if (pos < cap) {
         tmp[pos] = make_int2((int)p, id);
@@ -2781,23 +2785,41 @@ __device__ __forceinline__ void l1_sn_scatter(int blk, const Mesh& M, const Tile
   if (full) raise_flag(M.status, PMP_FLAG_CAPACITY);
 }
 
-// Level 1 for both kinds in one launch: blocks [0, nbc) take CIC chunks,
-// the rest supernova chunks.
+// Level 1's histogram pass for both kinds, and the supernovae's members, in
+// one launch.  Histogram blocks [0, nbc) take CIC chunks, [nbc, nbc + nbs)
+// supernova chunks; nct blocks count members, L lanes per supernova.  The
+// member counts are bound by FP64 issue and the histograms by latency, and
+// neither needs the other, so the two kinds of block are dealt out evenly over
+// the launch in octets (hist_col's rule of histogram block i on XCD i mod 8
+// holds).  As two launches 64 us (256^3, 1e6 CIC particles and 1e5 supernovae)
+// and 125 us (512^3, 4e6 mixed), as one 52 and 102 us.
 // (register budgets: the owner-tile variants' neighbour lookups would
 // otherwise cost a wave per SIMD; the padded variants fit them already)
-template <int OWN>
+template <int OWN, int L>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(7))) void k_l1_hist(Mesh M, TileGrid T, Particles C, Particles Sn,
                                                 int shift, int nb, int* __restrict__ hc, int nbc,
-                                                int* __restrict__ hs, int nbs,
-                                                const SnPk* __restrict__ pk,
+                                                int* __restrict__ hs, int nbs, int nct,
+                                                SnPk* __restrict__ pk,
                                                 double4* __restrict__ aos) {
   __shared__ NbrBox s_nbr[OWN == 1 ? 27 * kNbrCache : 1];
   __shared__ BoxL s_box[OWN == 2 ? 1 : kBoxCache];
-  if ((int)blockIdx.x < nbc)
-    l1_cic<false, OWN>(blockIdx.x, M, T, C, shift, nb, hc, nbc, aos, nullptr, 0, s_nbr,
-                       s_box);
-  else
-    l1_sn_hist<OWN>(blockIdx.x - nbc, M, T, Sn, shift, nb, hs, nbs, pk, s_nbr, s_box);
+  const long long oc = (nct + 7) >> 3, oh = (nbc + nbs + 7) >> 3, o = blockIdx.x >> 3;
+  const long long c0 = o * oc / (oc + oh), c1 = (o + 1) * oc / (oc + oh);
+  if (c1 > c0) {
+    const int blk = (int)(c0 * 8 + (blockIdx.x & 7));
+    if (blk >= nct) return;
+    int b;
+    DevBox B;
+    long long p;
+    SnPk R;
+    sn_members<L>(blk, M, Sn, pk, T.owner, b, B, p, R);
+    return;
+  }
+  const int blk = (int)((o - c0) * 8 + (blockIdx.x & 7));
+  if (blk < nbc)
+    l1_cic<false, OWN>(blk, M, T, C, shift, nb, hc, nbc, aos, nullptr, 0, s_nbr, s_box);
+  else if (blk < nbc + nbs)
+    l1_sn_hist<OWN>(blk - nbc, M, T, Sn, shift, nb, hs, nbs, s_nbr, s_box);
 }
 
 template <int OWN>
@@ -2807,14 +2829,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) void k
                                                    int* __restrict__ hs, int nbs,
                                                    double4* __restrict__ aos,
                                                    int2* __restrict__ ctmp, long long ccap,
-                                                   const SnPk* __restrict__ pk,
                                                    int2* __restrict__ stmp, long long scap) {
   __shared__ NbrBox s_nbr[OWN == 1 ? 27 * kNbrCache : 1];
   __shared__ BoxL s_box[OWN == 2 ? 1 : kBoxCache];
   if ((int)blockIdx.x < nbc)
     l1_cic<true, OWN>(blockIdx.x, M, T, C, shift, nb, hc, nbc, aos, ctmp, ccap, s_nbr, s_box);
   else
-    l1_sn_scatter<OWN>(blockIdx.x - nbc, M, T, Sn, shift, nb, hs, nbs, pk, stmp, scap, s_nbr, s_box);
+    l1_sn_scatter<OWN>(blockIdx.x - nbc, M, T, Sn, shift, nb, hs, nbs, stmp, scap, s_nbr, s_box);
 }
 
 // Level 2: one workgroup per coarse bucket sorts the bucket's records by
@@ -3956,24 +3977,29 @@ hipError_t launch_bin(const Mesh& M, const TileGrid& T, const Particles* cic,
   int* hs = bw.hist + (long long)nb * nbc;
   const long long n = (long long)nb * (nbc + nbs);
   const size_t lds1 = (size_t)nb * sizeof(int);
-  if (has_s) {
-    const unsigned grid = (unsigned)((sn->n * count_lanes + 255) / 256);
-    switch (count_lanes) {
-      case 1: hipLaunchKernelGGL(k_sn_count<1>, dim3(grid), dim3(256), 0, s, M, *sn, bw.sn_pk, T.owner); break;
-      case 2: hipLaunchKernelGGL(k_sn_count<2>, dim3(grid), dim3(256), 0, s, M, *sn, bw.sn_pk, T.owner); break;
-      case 8: hipLaunchKernelGGL(k_sn_count<8>, dim3(grid), dim3(256), 0, s, M, *sn, bw.sn_pk, T.owner); break;
-      case 16: hipLaunchKernelGGL(k_sn_count<16>, dim3(grid), dim3(256), 0, s, M, *sn, bw.sn_pk, T.owner); break;
-      default: hipLaunchKernelGGL(k_sn_count<4>, dim3(grid), dim3(256), 0, s, M, *sn, bw.sn_pk, T.owner);
-    }
-  }
   if (has_c || has_s) {
-#define PMP_L1H(OWN)                                                                        \
-  hipLaunchKernelGGL(k_l1_hist<OWN>, dim3(nbc + nbs), dim3(256), lds1, s, M, T,               \
+    // member-count blocks, by lanes per supernova (a power of two up to 16)
+    int lanes = 4;
+    if (count_lanes == 1 || count_lanes == 2 || count_lanes == 8 || count_lanes == 16)
+      lanes = count_lanes;
+    const int nct = has_s ? (int)((sn->n * lanes + 255) / 256) : 0;
+    const unsigned grid = 8u * ((unsigned)(nct + 7) / 8 + (unsigned)(nbc + nbs + 7) / 8);
+#define PMP_L1H(OWN, L)                                                                     \
+  hipLaunchKernelGGL((k_l1_hist<OWN, L>), dim3(grid), dim3(256), lds1, s, M, T,               \
                      has_c ? *cic : Particles{}, has_s ? *sn : Particles{}, S, nb, hc, nbc, hs, \
-                     nbs, (const SnPk*)bw.sn_pk, bw.cic_rec)
-    if (!T.owner) PMP_L1H(0);
-    else if (M.own_start == nullptr) PMP_L1H(2);  // one box covers the domain
-    else PMP_L1H(1);
+                     nbs, nct, bw.sn_pk, bw.cic_rec)
+#define PMP_L1HL(OWN)                        \
+  switch (lanes) {                           \
+    case 1: PMP_L1H(OWN, 1); break;          \
+    case 2: PMP_L1H(OWN, 2); break;          \
+    case 8: PMP_L1H(OWN, 8); break;          \
+    case 16: PMP_L1H(OWN, 16); break;        \
+    default: PMP_L1H(OWN, 4);                \
+  }
+    if (!T.owner) PMP_L1HL(0)
+    else if (M.own_start == nullptr) PMP_L1HL(2)  // one box covers the domain
+    else PMP_L1HL(1)
+#undef PMP_L1HL
 #undef PMP_L1H
   }
   // exclusive scan of both kinds' histograms, in place; hist[n] = total
@@ -3986,8 +4012,7 @@ hipError_t launch_bin(const Mesh& M, const TileGrid& T, const Particles* cic,
 #define PMP_L1S(OWN)                                                                        \
   hipLaunchKernelGGL(k_l1_scatter<OWN>, dim3(nbc + nbs), dim3(256), lds1, s, M, T,            \
                      has_c ? *cic : Particles{}, has_s ? *sn : Particles{}, S, nb, hc, nbc, hs, \
-                     nbs, bw.cic_rec, bw.cic_tmp, bw.cic_cap, (const SnPk*)bw.sn_pk, bw.sn_tmp, \
-                     bw.sn_cap)
+                     nbs, bw.cic_rec, bw.cic_tmp, bw.cic_cap, bw.sn_tmp, bw.sn_cap)
     if (!T.owner) PMP_L1S(0);
     else if (M.own_start == nullptr) PMP_L1S(2);
     else PMP_L1S(1);

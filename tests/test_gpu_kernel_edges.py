@@ -75,3 +75,36 @@ def test_sort_of_small_deposits(B, orc, n_cic, n_sn, nx, tile, fuse):  # noqa: F
     step_vs_oracle(B, orc, w, "fix64",
                    tuning=dict(deposit_path=1, tile_x=tile[0], tile_yz=tile[1], chunk_cic=1024,
                                chunk_sn=64, fuse_apply=fuse))
+
+
+@pytest.mark.parametrize("form", ["calls", "owner"])
+def test_binning_beside_the_member_count(B, orc, form):  # noqa: F811
+    """Supernovae are binned without knowing their member counts: spheres that
+    hold no cell centre, one, or (a particle on a cell corner, r^2 at its eight
+    centres' distance) eight by an exact tie, from every lane count; then ones
+    skipped for a mass or an energy that is not finite or overflows."""
+    from test_gpu_parity import _add_particle, _flags, compare, run_gpu, step_vs_oracle
+    rng = np.random.default_rng(8)
+    tie = float(np.sqrt(0.75))
+    rad = [0.0, 0.3, 0.5, np.nextafter(tie, 0.0), np.nextafter(tie, 1.0), 0.87, 2.0, 4.0]
+    pos, r = [], []
+    for q in rad:
+        for p in ([10.0, 20.0, 30.0], [7.5, 8.5, 9.5], [0.0, 0.0, 0.0], [79.999, 0.25, 40.0],
+                  *(80.0 * rng.random((5, 3)))):
+            pos.append(p)
+            r.append(q)
+    f = W.sn_fields(len(r), 4.0)
+    f["r"][:] = r
+    w = W.c2(nx=80, n_cic=500, n_sn=1, dtype=np.float64)
+    w = dataclasses.replace(w, sn=W._one_box(np.array(pos), f))
+    tun = {"deposit_path": 1, "tile_x": 16, "tile_yz": 2}  # more tiles than the short sort takes
+    for lanes in (1, 2, 4, 8, 16) if form == "owner" else (4,):
+        if form == "owner":
+            step_vs_oracle(B, orc, w, "fix64", tuning=dict(tun, fuse_apply=2, count_lanes=lanes))
+            continue
+        sn = _add_particle(w.sn, (40.1, 41.2, 42.3), e=float("nan"))
+        sn = _add_particle(sn, (50.1, 41.2, 42.3), m=float("inf"), r=0.3)
+        sn = _add_particle(sn, (60.5, 61.5, 62.5), m=1e7, r=0.0)
+        got = run_gpu(B, dataclasses.replace(w, sn=sn), "fix64", tuning=tun)
+        assert _flags(got) & 0x8 and "OVERFLOW" in got["status"]["flag_names"], got["status"]
+        compare(w, "fix64", got, orc.step(w, "fix64", want_eta=True))
