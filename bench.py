@@ -331,7 +331,8 @@ def snr_rate(B, reps=10):
             "regimes": {"MC": int((rm > 1).sum()), "ST": int(((rm > 0.027) & (rm <= 1)).sum()),
                         "EJ": int((rm <= 0.027).sum())},
             "kernel": "k_snr_deposit (one workgroup per remnant: 9^3 candidate cells x 4^3 "
-                      "sample points, twice; bound by the sample tests, not by memory)"}
+                      "sample points once, the covered cells then kept as a list; bound by "
+                      "scattered state lines and global atomics)"}
 
 
 def copy_gbps(B, nbytes=1 << 30, reps=10):
@@ -554,7 +555,7 @@ def measure(ctx, steps, warmup):
     return ms, eager_ms, spread, phases, ctx.status()
 
 
-KERNELS = {"bin": "k_sn_count+k_l1_*+k_scan_*+k_l2_*+k_units", "tile": "k_tile_deposit",
+KERNELS = {"bin": "k_l1_*+k_scan_*+k_l2_*+k_units", "tile": "k_tile_deposit",
            "zero": "k_zero", "cic": "k_cic_direct", "sn": "k_sn_direct",
            "sink_deposit": "k_sink_deposit", "fold": "k_fold", "sink_update": "k_sink_update",
            "apply": "k_apply"}
