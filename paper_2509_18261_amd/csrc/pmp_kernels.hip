@@ -3302,9 +3302,9 @@ __device__ __forceinline__ int image_shift(int code, int a, int glo, int D) {
 // applied.  Membership, shares and fixed-point remainders are the same as in
 // the direct kernels.
 //
-// What bounds it: with FP64 state the state's cache lines (512^3 FP64 moves
-// 6 GB in 1480 us, 4.1 TB/s; a kernel that only streams such a masked state
-// takes 1220 us); otherwise the latency of a tile's phases (metadata 1.9 us,
+// What bounds it: with FP64 state the state's cache lines and the gathered
+// records (512^3 FP64 moves 6.6 GB in 1400 to 1440 us, 4.6 TB/s; a kernel that
+// only streams such a masked state takes 1220 us); otherwise the latency of a tile's phases (metadata 1.9 us,
 // record gather 3.6, supernova rows 1.8, apply 5 of the 13 us of a 4096-box
 // tile), so what counts is resident wavefronts and loads in flight.  Hence
 // one instantiation per state type, 32-bit entry indices, one source-free
