@@ -3458,9 +3458,9 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(ACC == PMP
           const int u = c - G.glo[a];
           return (unsigned)u < (unsigned)G.ext[a] ? u : -1;
         };
-        l0[a] = local(i);
-        const int second = local(i + 1);
-        lh[a] = (int)floor(pos[a]) == i ? l0[a] : second;
+        const int first = local(i), second = local(i + 1);
+        lh[a] = (int)floor(pos[a]) == i ? first : second;
+        l0[a] = f[a] == 1.0 ? -1 : first;  // (f rounds to 1 one ulp below a cell centre)
         l1[a] = f[a] == 0.0 ? -1 : second;
       }
       // (m wx) wy of the four rows along z, then times wz and over V, the

@@ -30,3 +30,34 @@ def test_reproducibility_mode_relaunch(B):  # noqa: F811
     same = [float(np.mean(bufs[0][nz] == b[nz])) for b in bufs[1:]]
     print("identical on relaunch:", same, flush=True)
     assert min(same) >= 0.9945, same
+
+
+def test_weightless_corner_leaves_the_bound_alone(B, orc):  # noqa: F811
+    """Reproducibility mode: a particle one ulp below the first cell centre has
+    weight 1 - f = 0 in the cell beside it (f rounds to 1), so that cell's sum,
+    bound and truncation are those of the one particle that deposits there."""
+    import torch
+    rng = np.random.default_rng(6)
+    nx, g, k = 24, 2, 16
+    j, i = np.divmod(np.arange(k * k), k)
+    pos = np.empty((2 * k * k, 3))
+    pos[:, 1] = np.repeat(i + 0.5, 2)
+    pos[:, 2] = np.repeat(j + 0.5, 2)
+    pos[0::2, 0] = 0.1                       # deposits in cells -1 and 0
+    pos[1::2, 0] = np.nextafter(0.5, 0.0)    # deposits in cell 0 alone
+    m = rng.uniform(0.1, 1.0, len(pos))
+    domain, lo, n = W.single_box(nx)
+    w = W.Workload("weightless", domain, lo, n, g, 1.0,
+                   W.gas_state(rng, nx ** 3, np.float64).reshape(-1),
+                   cic=W._one_box(pos, {"m": m}))
+    ctx = B.Context(w, "f64r", channels="all")
+    ctx.set_tuning(deposit_path=1)
+    ctx.deposit()
+    torch.cuda.synchronize()
+    p = nx + 2 * g
+    got = ctx.buf.cpu().numpy()[:p ** 3].reshape(p, p, p)
+    ctx.close()
+    ref = np.asarray(orc.deposit(w, "f64r")[0])[:p ** 3].reshape(p, p, p)
+    cells = (slice(g, g + k), slice(g, g + k), g - 1)
+    assert (ref[cells] > 0).all()
+    assert np.array_equal(got[cells], ref[cells]), int((got[cells] != ref[cells]).sum())
