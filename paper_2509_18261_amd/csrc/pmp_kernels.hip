@@ -3076,12 +3076,18 @@ __global__ __launch_bounds__(256) void k_units(TileGrid T, const int* __restrict
 // such a sort.  k_small_count finds the supernovae's members, counts each
 // tile's entries (an LDS histogram over all tiles, then one global atomic per
 // tile a block met, which reserves the block's entries of that tile) and
-// writes every particle's (tile, rank within the tile) pairs into its own
-// slots, ended by tile -1; k_small_scan turns the counts into offsets and
-// claims the chunk slots of split tiles; k_small_fill writes the lists.
+// writes every particle's (tile, rank within the tile) pairs: a CIC particle's
+// into its own eight slots, ended by tile -1, a block's supernovae's into a
+// part of one list, claimed past the parts of the blocks before (a slot range
+// per supernova would cut off the one whose radius exceeds the declared
+// bound, where the list as a whole still holds its entries).  k_small_scan
+// turns the counts into offsets and claims the chunk slots of split tiles;
+// k_small_fill writes the lists.
 // 32^3 with 16 particles: the sort takes 16 us instead of 37, the step 33
 // instead of 54; 101 x 83 x 67 with 36302: 38 instead of 62, 63 instead of 86.
 constexpr int kSmallLanes = 4;  // lanes per supernova
+// a supernova's pair is its index and (tile << 16 | rank)
+static_assert(kSmallTiles <= 1 << 15 && kSmallEntries / 8 <= 1 << 16, "pair bits");
 
 template <int OWN>
 __global__ __launch_bounds__(256) void k_small_count(Mesh M, TileGrid T, Particles C, Particles Sn,
@@ -3089,8 +3095,10 @@ __global__ __launch_bounds__(256) void k_small_count(Mesh M, TileGrid T, Particl
                                                      double4* __restrict__ aos,
                                                      int2* __restrict__ cpair,
                                                      SnPk* __restrict__ pk,
-                                                     int2* __restrict__ spair, int sslots) {
+                                                     int2* __restrict__ spair, int scap) {
   extern __shared__ int h[];
+  __shared__ int s_total, s_base;  // the block's supernova entries, and their place
+  if (threadIdx.x == 0) s_total = 0;
   const int nt = (int)T.ntiles;
   for (int t = threadIdx.x; t < nt; t += blockDim.x) h[t] = 0;
   const int g = M.ghost;
@@ -3100,8 +3108,7 @@ __global__ __launch_bounds__(256) void k_small_count(Mesh M, TileGrid T, Particl
   long long p = 0;
   DevBox B;
   bool live = false;
-  int2* slot = nullptr;
-  int cap = 8;
+  int2* slot = nullptr;  // where the particle's pairs go
   int* cnt = count;
   if (cic) {
     const long long p0 = (long long)blockIdx.x * 256, p1 = min(p0 + 256, C.n);
@@ -3124,9 +3131,7 @@ __global__ __launch_bounds__(256) void k_small_count(Mesh M, TileGrid T, Particl
     SnPk R;
     N = sn_members<kSmallLanes>(blockIdx.x - nbc, M, Sn, pk, T.owner, b, B, p, R);
     cnt = count + nt;
-    cap = sslots;
     if (p < Sn.n && (threadIdx.x & (kSmallLanes - 1)) == 0) {
-      slot = spair + (long long)sslots * p;
       live = N != 0;
       if (N < 0) {
         const double q[3] = {R.x, R.y, R.z};
@@ -3137,24 +3142,42 @@ __global__ __launch_bounds__(256) void k_small_count(Mesh M, TileGrid T, Particl
     }
   }
   __syncthreads();
-  // how many of the block's entries each tile gets
-  int n = 0;
-  if (live)
-    particle_tiles<OWN>(M, T, b, B, lo, hi, [&](int t) {
-      if (n++ < cap) atomicAdd(h + t, 1);
-    });
-  if (n > cap) flag |= PMP_FLAG_CAPACITY;
-  __syncthreads();
+  // how many of the block's entries each tile gets; twice where the supernova
+  // list ends within the block's part, the second time those below its end
+  int n = 0, room = cic ? 8 : 0x7fffffff;  // (2^3 cells meet at most eight tiles)
+  for (int round = 0; round < 2; ++round) {
+    n = 0;
+    if (live)
+      particle_tiles<OWN>(M, T, b, B, lo, hi, [&](int t) {
+        if (n++ < room) atomicAdd(h + t, 1);
+      });
+    int at = 0;
+    if (!cic && round == 0 && n > 0) at = atomicAdd(&s_total, n);
+    __syncthreads();
+    if (cic || round == 1) break;
+    if (threadIdx.x == 0) s_base = atomicAdd(count + 2 * nt, s_total);
+    __syncthreads();
+    at += s_base;
+    slot = spair + at;
+    if (s_base + s_total <= scap) break;
+    room = min(max(scap - at, 0), n);
+    if (room < n) flag |= PMP_FLAG_CAPACITY;
+    for (int t = threadIdx.x; t < nt; t += blockDim.x) h[t] = 0;
+    __syncthreads();
+  }
   for (int t = threadIdx.x; t < nt; t += blockDim.x)
     if (h[t]) h[t] = atomicAdd(cnt + t, h[t]);
   __syncthreads();
   n = 0;
   if (live)
     particle_tiles<OWN>(M, T, b, B, lo, hi, [&](int t) {
-      if (n < cap) slot[n] = make_int2(t, atomicAdd(h + t, 1));
+      if (n < room) {
+        const int rank = atomicAdd(h + t, 1);
+        slot[n] = cic ? make_int2(t, rank) : make_int2((int)p, t << 16 | rank);
+      }
       ++n;
     });
-  if (slot && n < cap) slot[n] = make_int2(-1, 0);
+  if (cic && slot && n < 8) slot[n] = make_int2(-1, 0);
   if (flag) raise_flag(M.status, flag);
 }
 
@@ -3211,35 +3234,41 @@ __global__ __launch_bounds__(1024) void k_small_scan(int nt, const int* __restri
   }
 }
 
-__global__ __launch_bounds__(256) void k_small_fill(long long n_cic, long long n_sn, int nbc,
+__global__ __launch_bounds__(256) void k_small_fill(long long n_cic, int nbc,
                                                     const int2* __restrict__ cpair,
-                                                    const int2* __restrict__ spair, int sslots,
+                                                    const int2* __restrict__ spair,
+                                                    const int* __restrict__ sn_total, int scap,
                                                     const int* __restrict__ coff,
                                                     const int* __restrict__ soff,
                                                     int* __restrict__ cidx,
                                                     int* __restrict__ sidx) {
-  const bool cic = (int)blockIdx.x < nbc;
-  const long long p = (long long)((int)blockIdx.x - (cic ? 0 : nbc)) * 256 + threadIdx.x;
-  if (p >= (cic ? n_cic : n_sn)) return;
-  const int cap = cic ? 8 : sslots;
-  const int2* slot = (cic ? cpair : spair) + (long long)cap * p;
-  const int* off = cic ? coff : soff;
-  int* idx = cic ? cidx : sidx;
+  if ((int)blockIdx.x >= nbc) {  // supernova entries, one per thread
+    const int total = min(*sn_total, scap);
+    for (int e = ((int)blockIdx.x - nbc) * 256 + (int)threadIdx.x; e < total;
+         e += ((int)gridDim.x - nbc) * 256) {
+      const int2 v = spair[e];
+      sidx[soff[v.y >> 16] + (v.y & 0xffff)] = v.x;
+    }
+    return;
+  }
+  const long long p = (long long)blockIdx.x * 256 + threadIdx.x;
+  if (p >= n_cic) return;
+  const int2* slot = cpair + 8 * p;
   // four pairs at a time: their loads, then their offsets' loads, together
-  for (int j = 0; j < cap; j += 4) {
+  for (int j = 0; j < 8; j += 4) {
     int2 v[4];
     int o[4];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) v[q] = j + q < cap ? slot[j + q] : make_int2(-1, 0);
+    for (int q = 0; q < 4; ++q) v[q] = slot[j + q];
     // (slots past the end mark were not written this time)
 #pragma unroll
     for (int q = 1; q < 4; ++q)
       if (v[q - 1].x < 0) v[q].x = -1;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) o[q] = v[q].x >= 0 ? off[v[q].x] : 0;
+    for (int q = 0; q < 4; ++q) o[q] = v[q].x >= 0 ? coff[v[q].x] : 0;
 #pragma unroll
     for (int q = 0; q < 4; ++q)
-      if (v[q].x >= 0) idx[o[q] + v[q].y] = (int)p;
+      if (v[q].x >= 0) cidx[o[q] + v[q].y] = (int)p;
     if (v[3].x < 0) break;
   }
 }
@@ -3960,8 +3989,9 @@ static hipError_t launch_bin_small(const Mesh& M, const TileGrid& T, const Parti
                                    hipStream_t s) {
   const bool has_c = cic && cic->n > 0, has_s = sn && sn->n > 0;
   const int nt = (int)T.ntiles;
-  int* count = bw.hist2;  // [2 ntiles]: both kinds
-  hipError_t e = launch_zero(count, 2ll * nt * (long long)sizeof(int), 256, s);
+  int* count = bw.hist2;  // [2 ntiles + 1]: both kinds, and the supernova list's length
+  const int scap = (int)bw.sn_cap;
+  hipError_t e = launch_zero(count, (2ll * nt + 1) * (long long)sizeof(int), 256, s);
   if (e != hipSuccess) return e;
   const int nbc = has_c ? (int)((cic->n + 255) / 256) : 0;
   const int per = 256 / kSmallLanes;
@@ -3969,7 +3999,7 @@ static hipError_t launch_bin_small(const Mesh& M, const TileGrid& T, const Parti
 #define PMP_SMALL(OWN)                                                                        \
   hipLaunchKernelGGL(k_small_count<OWN>, dim3(nbc + nbs), dim3(256), nt * sizeof(int), s, M,  \
                      T, has_c ? *cic : Particles{}, has_s ? *sn : Particles{}, nbc, count,    \
-                     bw.cic_rec, bw.cic_tmp, bw.sn_pk, bw.sn_tmp, bw.sn_slots)
+                     bw.cic_rec, bw.cic_tmp, bw.sn_pk, bw.sn_tmp, scap)
   if (!T.owner) PMP_SMALL(0);
   else if (M.own_start == nullptr) PMP_SMALL(2);  // one box covers the domain
   else PMP_SMALL(1);
@@ -3980,10 +4010,12 @@ static hipError_t launch_bin_small(const Mesh& M, const TileGrid& T, const Parti
                      t.chunk_cic, t.chunk_sn, chunk_share(M), bw.heavy_base,
                      bw.heavy_unit, bw.heavy_count, bw.arrive,
                      chunk_slots(cic, sn, bw, t));
-  const int nfs = has_s ? (int)((sn->n + 255) / 256) : 0;
-  hipLaunchKernelGGL(k_small_fill, dim3(nbc + nfs), dim3(256), 0, s, has_c ? cic->n : 0,
-                     has_s ? sn->n : 0, nbc, (const int2*)bw.cic_tmp, (const int2*)bw.sn_tmp,
-                     bw.sn_slots, (const int*)coff, (const int*)soff, bw.cic_idx, bw.sn_rec);
+  // (about eight entries per supernova; the blocks walk what there is)
+  const int nfs = has_s ? (int)((8 * sn->n + 255) / 256) : 0;
+  hipLaunchKernelGGL(k_small_fill, dim3(nbc + nfs), dim3(256), 0, s, has_c ? cic->n : 0, nbc,
+                     (const int2*)bw.cic_tmp, (const int2*)bw.sn_tmp,
+                     (const int*)(count + 2 * nt), scap, (const int*)coff, (const int*)soff,
+                     bw.cic_idx, bw.sn_rec);
   return hipGetLastError();
 }
 

@@ -61,3 +61,27 @@ def test_weightless_corner_leaves_the_bound_alone(B, orc):  # noqa: F811
     cells = (slice(g, g + k), slice(g, g + k), g - 1)
     assert (ref[cells] > 0).all()
     assert np.array_equal(got[cells], ref[cells]), int((got[cells] != ref[cells]).sum())
+
+
+@pytest.mark.parametrize("fuse", [0, 2])
+@pytest.mark.parametrize("nx", [40, 96])
+def test_radius_above_the_declared_bound(B, orc, nx, fuse):  # noqa: F811
+    """A few supernovae wider than the declared r_max: the entry list as a
+    whole holds theirs too, so nothing is cut off and no flag is raised (both
+    sorts: 40^3 has few enough tiles for the short one, 96^3 does not)."""
+    import dataclasses
+    import torch
+    w = W.c2(nx=nx, n_cic=400, n_sn=400, dtype=np.float64)
+    f = dict(w.sn.fields)
+    f["r"] = np.where(np.arange(w.sn.n) % 20 == 0, 4.0, 1.0)
+    w = dataclasses.replace(w, sn=W.Particles(f, w.sn.box_off))
+    ctx = B.Context(w, "fix64", channels="all")
+    ctx.set_tuning(deposit_path=1, tile_x=16, tile_yz=2, fuse_apply=fuse)
+    ctx.sn.r_max = 1.0
+    ctx.step()
+    torch.cuda.synchronize()
+    st = ctx.status()
+    got = ctx.state.cpu().numpy()
+    ctx.close()
+    assert st["flags"] in (0, 0x10), st
+    assert np.array_equal(got, orc.step(w, "fix64")["state"])
