@@ -693,7 +693,7 @@ template <class T> int regrow(T** p, long long have, long long need) {
 // Sizes (elements) of the binned-deposit scratch arrays for these particle
 // counts and the current tiles.
 struct BinSizes {
-  int shift = 0, nb = 0, sn_slots = 1;
+  int shift = 0, nb = 0, sn_slots = 1, sn_tiles = 1;
   long long hist = 0, blocks = 0, tiles1 = 0, partial = 0, slot_cap = 0, cic_cap = 0,
             sn_cap = 0, hist2 = 0, blocks2 = 0, slice_base = 0, n_sn = 0, n_cic = 0;
 };
@@ -731,6 +731,9 @@ int bin_sizes(const pmp_ctx* c, long long n_cic, long long n_sn, double r_max, B
   const long long cic_cap = std::max<long long>(8 * n_cic, 1);
   const long long sn_cap = std::max<long long>(maxt * n_sn, 1);
   z.sn_slots = (int)std::min<long long>(maxt, 1 << 30);
+  double mean = 1.0;  // a span of 2 r on tiles of t cells meets 2 r / t + 1 of them
+  for (int a = 0; a < 3; ++a) mean *= 2.0 * std::max(r_max, 0.0) / t[a] + 1.0;
+  z.sn_tiles = (int)std::ceil(std::min(mean, 1e6));
   const long long full_slices = (cic_cap + kSlice - 1) / kSlice + (sn_cap + kSlice - 1) / kSlice;
   // coarse buckets of 2^shift consecutive tiles: at most 512 buckets, or 1024
   // where that would put more than 256 tiles in one (sized for the padded
@@ -806,6 +809,7 @@ size_t carve_bin(const BinSizes& z, char* base, BinWork* w) {
     W.slot_cap = z.slot_cap;
     W.shift = z.shift;
     W.sn_slots = z.sn_slots;
+    W.sn_tiles = z.sn_tiles;
     W.nbuckets = z.nb;
     W.max_slices = (z.hist2 - 1) >> z.shift;
   }
@@ -835,6 +839,7 @@ int ensure_bin_work(pmp_ctx* c, long long n_cic, long long n_sn, double r_max, h
                   sn_cap = z.sn_cap;
   c->bw.shift = shift;
   c->bw.sn_slots = z.sn_slots;
+  c->bw.sn_tiles = z.sn_tiles;
   c->bw.nbuckets = nb;
   const bool grow = hist > c->bw_hist || blocks > c->bw_blocks || c->ntiles + 1 > c->bw_tiles ||
                     cic_cap > c->bw.cic_cap || sn_cap > c->bw.sn_cap || n_sn > c->bw_nsn ||

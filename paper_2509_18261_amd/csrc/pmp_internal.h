@@ -216,6 +216,7 @@ struct BinWork {
   int* sn_off;          // [ntiles + 1]
   SnPk* sn_pk;          // [n_sn]
   int sn_slots;         // entry capacity per supernova: the most tiles one can touch
+  int sn_tiles;         // tiles one of the largest radius touches on average
   long long cic_cap, sn_cap;
   // level 2 works on slices of at most kSlice records of one bucket
   int* slice_base;      // [2 * nbuckets + 1]: first slice of each (kind, bucket)
@@ -235,13 +236,24 @@ struct BinWork {
 };
 
 constexpr int kSlice = 4096;
-// Deposits sorted by k_small_count: at most this many tiles (an LDS histogram
-// of 32 KB) and CIC particles plus 8 per supernova.  Beyond that the two-level
-// sort is as fast: whole steps at 128^3 FP64 take 80 us with this sort and 91
-// with the other for 100000 CIC particles and 10000 supernovae, 107 and 100
-// for twice as many, 82 and 81 for 200000 CIC particles alone.
-constexpr long long kSmallTiles = 8192;
+// Deposits sorted by k_small_count.  Whole steps in FP64, this sort against the
+// two-level one in us:
+//   tiles (every block clears and walks a histogram of them all, one block
+//     scans them): 2048 tiles 65 and 75, 4096 tiles 76 and 79 (20000 CIC
+//     particles, 2000 supernovae), 91 and 89 (100000 and 12000), 8192 tiles 102
+//     and 90, 113 and 96;
+//   tiles a supernova touches (one lane lists them, twice): 22 tiles 111 and
+//     111, 37 tiles 172 and 165, 71 tiles 294 and 265 (5000 supernovae on owner
+//     tiles);
+//   CIC particles plus 8 per supernova: 1352 tiles, 60 and 72 for 36000, 79 and
+//     83 for 196000.
+constexpr long long kSmallTiles = 4096;
 constexpr long long kSmallEntries = 200000;
+constexpr int kSmallSnTiles = 32;
+inline bool small_deposit(long long ntiles, long long n_cic, long long n_sn, int sn_tiles) {
+  return ntiles <= kSmallTiles && n_cic + 8 * n_sn <= kSmallEntries &&
+         (n_sn == 0 || sn_tiles <= kSmallSnTiles);
+}
 
 // Supernova entries per batch of the tile pass: one per lane of a wavefront.
 constexpr int kTileSnBatch = 64;

@@ -4026,8 +4026,8 @@ hipError_t launch_bin(const Mesh& M, const TileGrid& T, const Particles* cic,
   // (not in the reproducibility mode: its truncation follows the order of the
   // additions, and the short sort's order of entries varies from run to run
   // where the two-level sort's, with ordered turns in level 2, hardly does)
-  if (M.acc != PMP_ACC_F64R && T.ntiles <= kSmallTiles &&
-      (has_c ? cic->n : 0) + 8 * (has_s ? sn->n : 0) <= kSmallEntries)
+  if (M.acc != PMP_ACC_F64R &&
+      small_deposit(T.ntiles, has_c ? cic->n : 0, has_s ? sn->n : 0, bw.sn_tiles))
     return launch_bin_small(M, T, cic, sn, bw, t, s);
   const int nbc = has_c ? (int)((cic->n + kBinChunkCic - 1) / kBinChunkCic) : 0;
   const int nbs = has_s ? (int)((sn->n + kBinChunkSn - 1) / kBinChunkSn) : 0;

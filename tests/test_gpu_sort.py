@@ -85,3 +85,36 @@ def test_radius_above_the_declared_bound(B, orc, nx, fuse):  # noqa: F811
     ctx.close()
     assert st["flags"] in (0, 0x10), st
     assert np.array_equal(got, orc.step(w, "fix64")["state"])
+
+
+def padded_tiles(n, g, tx, tyz):
+    """Tiles of one box on the ghost-zoned grid (x tiles sit on owned cells)."""
+    c = lambda a, b: -(-a // b)  # noqa: E731
+    return c(n[0], tx) * c(n[1] + 2 * g, tyz) * c(n[2] + 2 * g, tyz)
+
+
+def owner_tiles(n, tx, tyz):
+    return padded_tiles(n, 0, tx, tyz)
+
+
+@pytest.mark.parametrize("dims,fuse,radius", [
+    ((64, 64, 64), 2, 3.0), ((64, 64, 66), 2, 3.0),  # owner grid: 4096 and 4224 tiles
+    ((64, 56, 56), 0, 3.0), ((64, 56, 58), 0, 3.0),  # padded grid: the same
+    ((48, 40, 40), 0, 3.5), ((48, 40, 40), 0, 3.75),  # 30 and 34 tiles per supernova
+    ((48, 40, 40), 2, 3.5), ((48, 40, 40), 2, 3.75),
+])
+def test_edges_of_the_short_sort(B, orc, dims, fuse, radius):  # noqa: F811
+    """Deposits on either side of the limits (4096 tiles, 32 tiles touched by a
+    supernova) between the short sort and the two-level one."""
+    from test_gpu_parity import step_vs_oracle
+    rng = np.random.default_rng(12)
+    tiles = owner_tiles(dims, 16, 2) if fuse == 2 else padded_tiles(dims, 4, 16, 2)
+    if radius == 3.0:
+        assert tiles == (4096 if dims[2] % 32 in (0, 24) else 4224)
+    domain, lo, n = W.single_box(*dims)
+    w = W.Workload("edges", domain, lo, n, 4, 1.0,
+                   W.gas_state(rng, int(np.prod(dims)), np.float64).reshape(-1),
+                   cic=W._one_box(W.uniform_positions(rng, 3000, dims), W.cic_fields(rng, 3000)),
+                   sn=W._one_box(W.uniform_positions(rng, 300, dims), W.sn_fields(300, radius)))
+    step_vs_oracle(B, orc, w, "fix64", tuning=dict(deposit_path=1, tile_x=16, tile_yz=2,
+                                                   fuse_apply=fuse))
