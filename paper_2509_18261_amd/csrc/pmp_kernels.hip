@@ -4276,11 +4276,15 @@ static void snr_dep(const Mesh& M, SnrArgs A, const void* state, void* buf, doub
   A.side = snr_side(A.r_k);
   const int grid = grid_for(A.n, 1, 65536);
   // one wavefront per remnant once there are more remnants than four-wavefront
-  // workgroups fit the chip: the remnant's scalars and reductions are then
-  // computed by one wavefront instead of four (417 against 446 us for 20000
-  // remnants); fewer remnants finish sooner with four
+  // workgroups fit the chip, while the kernel is small: the remnant's scalars
+  // and reductions are then computed by one wavefront instead of four.  Wider
+  // kernels fill a compute unit's LDS with their tables and lists before it has
+  // enough wavefronts of this kind.  FP64, one and four wavefronts, 12000
+  // remnants, sub = 4, in us: r_K = 3 185 and 210, 4 349 and 357, 5 599 and
+  // 538, 8 2718 and 1602; sub = 1: 124 and 142, 246 and 263, 425 and 412, 1574
+  // and 1324; 300 remnants finish sooner with four at any radius
   const size_t lds = snr_lds_bytes(A.sub, A.side, A.list_cap);
-  if (A.n > 8ll * M.num_cu)
+  if (A.n > 8ll * M.num_cu && A.r_k <= 4.5)
     hipLaunchKernelGGL((k_snr_deposit<ACC, S, kWave>), dim3(grid), dim3(kWave), lds, s, M, A,
                        (const S*)state, (typename AccT<ACC>::T*)buf, info);
   else

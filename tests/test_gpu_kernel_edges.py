@@ -108,3 +108,15 @@ def test_binning_beside_the_member_count(B, orc, form):  # noqa: F811
         got = run_gpu(B, dataclasses.replace(w, sn=sn), "fix64", tuning=tun)
         assert _flags(got) & 0x8 and "OVERFLOW" in got["status"]["flag_names"], got["status"]
         compare(w, "fix64", got, orc.step(w, "fix64", want_eta=True))
+
+
+@pytest.mark.parametrize("acc", ["fix64", "f64"])
+@pytest.mark.parametrize("r_k,sub", [(0.3, 2), (3.0, 4), (4.5, 2), (4.75, 2), (8.25, 1)])
+def test_snr_many_remnants(B, orc, r_k, sub, acc):  # noqa: F811
+    """More remnants than workgroups of four wavefronts fit the chip, on either
+    side of the radius up to which one wavefront takes a whole remnant, and
+    with kernels too wide for a cell list."""
+    w = W.snr_box(nx=40, n_snr=2100, seed=33, dtype=np.float64)
+    w = dataclasses.replace(w, name=f"many_r{r_k}_s{sub}", ghost=10,
+                            snr_params=dataclasses.replace(w.snr_params, r_k=r_k, sub=sub))
+    check(B, orc, w, acc)
