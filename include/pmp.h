@@ -236,8 +236,8 @@ typedef struct {
                             this many, each accumulated in LDS by its own
                             workgroup; the last chunk to finish sums the
                             chunks' partial tiles in chunk order and stores
-                            (a tile holding more than one workgroup's share of
-                            all entries is split into smaller chunks) */
+                            (a tile holding two workgroups' shares of all
+                            entries or more is split into smaller chunks) */
   int32_t chunk_sn;      /* the same threshold for supernova entries (16 .. 2^24) */
   int32_t fuse_apply;    /* 1: pmp_step without sinks on the binned path applies
                             Steps 3 + 5 inside the tile pass for owned cells at

@@ -11,6 +11,7 @@
 #include <string>
 #include <vector>
 
+#include "pmp_chunks.h"
 #include "pmp_internal.h"
 
 using namespace pmp;
@@ -757,7 +758,7 @@ int bin_sizes(const pmp_ctx* c, long long n_cic, long long n_sn, double r_max, B
   z.hist2 = (max_slices << shift) + 1;
   z.blocks2 = (z.hist2 + 1023) / 1024 + 1;
   // chunk slots for split tiles, each holding two channels of a padded LDS tile
-  z.slot_cap = 4ll * c->num_cu;
+  z.slot_cap = (long long)kSlotsPerCu * c->num_cu;
   z.partial = z.slot_cap * 2 * (long long)(t[0] + 2 * c->ghost + 1) * t[1] * t[2];
   z.cic_cap = cic_cap;
   z.sn_cap = sn_cap;

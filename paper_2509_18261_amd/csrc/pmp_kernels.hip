@@ -12,6 +12,7 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "pmp_chunks.h"
 #include "pmp_internal.h"
 
 namespace pmp {
@@ -3019,27 +3020,6 @@ __global__ __launch_bounds__(256) void k_l2_scatter(L2Geom G, const int* __restr
   }
 }
 
-// Chunks a tile's entries are split into: at most cc CIC and cs supernova
-// entries per chunk, and no more than a workgroup's share of the deposit's
-// nct and nst entries (total / share, but at least kChunkMin entries; up to
-// kChunksMost chunks on that account), so that a cluster's core, which may
-// hold a fifth of all particles in one tile, is spread over the chip.  1e6
-// Plummer particles at 256^3 FP64 on 16 x 8 x 8 tiles with cc = 16384: the step
-// with 256 sinks takes 270 us with whole chunks of cc behind device-scope
-// fences, 230 us without the fences (see the partial sums in the tile pass),
-// 202 us with the share; shares of one, two or four workgroups per compute
-// unit differ by 3%.
-constexpr int kChunkMinCic = 1024, kChunkMinSn = 128, kChunksMost = 32;
-__device__ __forceinline__ int tile_chunks(long long nc, long long ns, int cc, int cs,
-                                           long long nct, long long nst, int share) {
-  if (share <= 0) return 1;  // never split
-  const long long ec = max((long long)kChunkMinCic, nct / share);
-  const long long es = max((long long)kChunkMinSn, nst / share);
-  const long long want = min(max((nc + ec - 1) / ec, (ns + es - 1) / es), (long long)kChunksMost);
-  const long long need = max((nc + cc - 1) / cc, (ns + cs - 1) / cs);
-  return (int)max(1ll, max(want, need));
-}
-
 // One thread per tile: tiles with more entries than a chunk holds claim
 // consecutive chunk slots (when slots remain) and list their chunks (tile,
 // chunk, chunks).  The sorted lists hold no entry past the capacity.
@@ -3958,7 +3938,7 @@ hipError_t launch_cic_direct(const Mesh& M, const Particles& P, void* buf, int b
 // Workgroups a deposit's entries are shared over before tiles are split (see
 // tile_chunks); 0 in the reproducibility mode, which never splits a tile: each
 // tile sums all of its cells' contributions (and their bounds).
-static int chunk_share(const Mesh& M) { return M.acc == PMP_ACC_F64R ? 0 : 2 * M.num_cu; }
+static int chunk_share(const Mesh& M) { return M.acc == PMP_ACC_F64R ? 0 : kSharesPerCu * M.num_cu; }
 
 // Chunk slots a deposit can need: a tile is split only past a chunk's length,
 // so its chunks number at most twice its entries over that length.
