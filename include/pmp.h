@@ -262,7 +262,11 @@ typedef struct {
                             the step runs as with 1. */
   int32_t count_lanes;   /* binned path: lanes counting one supernova's sphere
                             members (its candidate rows dealt round them):
-                            1, 2, 4, 8 or 16 */
+                            1, 2, 4, 8 or 16.  Deposits that take the sort of
+                            small deposits (at most 4096 tiles, 32 tiles per
+                            supernova and n_cic + 8 n_sn = 200000, not
+                            PMP_ACC_F64R) always use 4, and the tuner then
+                            leaves this field alone */
 } pmp_tuning;
 
 /* Create a context on the current HIP device.  Copies the layout, checks the

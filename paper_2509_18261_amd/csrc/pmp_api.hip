@@ -1942,9 +1942,14 @@ int pmp_autotune(pmp_ctx* c, void* state, void* buf, const pmp_cic* cic, const p
       t.tile_grid_per_cu = gpc;
       time_one(t);
     }
-    if (has_sn) {
-      // lanes per supernova in the member count (large spheres want more)
-      const pmp_tuning w3 = best_t;
+    // lanes per supernova in the member count (large spheres want more); the
+    // sort of small deposits has its own number
+    const pmp_tuning w3 = best_t;
+    const long long n_cic = cic ? cic->n : 0;
+    BinSizes z;
+    if (has_sn && rc == PMP_OK && pmp_set_tuning(c, &w3) == PMP_OK &&
+        bin_sizes(c, n_cic, sn->n, sn->r_max, z) == PMP_OK &&
+        !small_deposit(c->acc, c->tiles(owner_step(c)).ntiles, n_cic, sn->n, z.sn_tiles)) {
       for (int lanes : {1, 2, 4, 8, 16}) {
         if (lanes == w3.count_lanes) continue;
         pmp_tuning t = w3;

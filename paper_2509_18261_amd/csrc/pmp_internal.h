@@ -250,8 +250,12 @@ constexpr int kSlice = 4096;
 constexpr long long kSmallTiles = 4096;
 constexpr long long kSmallEntries = 200000;
 constexpr int kSmallSnTiles = 32;
-inline bool small_deposit(long long ntiles, long long n_cic, long long n_sn, int sn_tiles) {
-  return ntiles <= kSmallTiles && n_cic + 8 * n_sn <= kSmallEntries &&
+// Not in the reproducibility mode: its truncation follows the order of the
+// additions, and the short sort's order of entries varies from run to run
+// where the two-level sort's, with ordered turns in level 2, hardly does.
+inline bool small_deposit(int acc, long long ntiles, long long n_cic, long long n_sn,
+                          int sn_tiles) {
+  return acc != PMP_ACC_F64R && ntiles <= kSmallTiles && n_cic + 8 * n_sn <= kSmallEntries &&
          (n_sn == 0 || sn_tiles <= kSmallSnTiles);
 }
 

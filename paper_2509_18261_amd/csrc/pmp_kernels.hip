@@ -4003,11 +4003,7 @@ hipError_t launch_bin(const Mesh& M, const TileGrid& T, const Particles* cic,
                       const Particles* sn, BinWork& bw, const pmp_tuning& t, hipStream_t s) {
   const int nb = bw.nbuckets, S = bw.shift, count_lanes = t.count_lanes;
   const bool has_c = cic && cic->n > 0, has_s = sn && sn->n > 0;
-  // (not in the reproducibility mode: its truncation follows the order of the
-  // additions, and the short sort's order of entries varies from run to run
-  // where the two-level sort's, with ordered turns in level 2, hardly does)
-  if (M.acc != PMP_ACC_F64R &&
-      small_deposit(T.ntiles, has_c ? cic->n : 0, has_s ? sn->n : 0, bw.sn_tiles))
+  if (small_deposit(M.acc, T.ntiles, has_c ? cic->n : 0, has_s ? sn->n : 0, bw.sn_tiles))
     return launch_bin_small(M, T, cic, sn, bw, t, s);
   const int nbc = has_c ? (int)((cic->n + kBinChunkCic - 1) / kBinChunkCic) : 0;
   const int nbs = has_s ? (int)((sn->n + kBinChunkSn - 1) / kBinChunkSn) : 0;

@@ -118,3 +118,16 @@ def test_edges_of_the_short_sort(B, orc, dims, fuse, radius):  # noqa: F811
                    sn=W._one_box(W.uniform_positions(rng, 300, dims), W.sn_fields(300, radius)))
     step_vs_oracle(B, orc, w, "fix64", tuning=dict(deposit_path=1, tile_x=16, tile_yz=2,
                                                    fuse_apply=fuse))
+
+
+def test_tuner_leaves_lanes_the_short_sort_ignores(B):  # noqa: F811
+    """Where the short sort runs, with its own number of lanes per supernova,
+    the tuner does not choose among lane counts that make no difference."""
+    from paper_2509_18261_amd import autotune
+    for seed in (2, 3, 4):
+        ctx = B.Context(W.c2(seed=seed, nx=104), "fix64", channels="auto")
+        before = ctx.tuning().as_dict()["count_lanes"]
+        tuned = autotune.tune(ctx, cache_path=None)["tuning"]
+        ctx.close()
+        print("tuned:", tuned, flush=True)
+        assert tuned["count_lanes"] == before
