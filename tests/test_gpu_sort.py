@@ -131,3 +131,184 @@ def test_tuner_leaves_lanes_the_short_sort_ignores(B):  # noqa: F811
         ctx.close()
         print("tuned:", tuned, flush=True)
         assert tuned["count_lanes"] == before
+
+
+# ------------------------------------------------- the two-level sort
+# (deposits past the short sort's limits: over 4096 tiles, or more than 200000
+# CIC particles plus 8 per supernova)
+
+SMALL_TILES, SMALL_ENTRIES = 4096, 200000
+
+
+def entries(w):
+    return (w.cic.n if w.cic else 0) + 8 * (w.sn.n if w.sn else 0)
+
+
+def repeat_in_boxes(P, times):
+    """Every box's particles `times` over, in turn, so that a block of the sort
+    meets all of them."""
+    idx = [np.tile(np.arange(a, b), times) for a, b in zip(P.box_off[:-1], P.box_off[1:])]
+    idx = np.concatenate(idx)
+    return W.Particles({k: v[idx].copy() for k, v in P.fields.items()}, P.box_off * times)
+
+
+@pytest.mark.parametrize("lanes", [1, 4, 16])
+@pytest.mark.parametrize("shape", [(16, 4), (32, 2)])
+@pytest.mark.parametrize("kind", ["three", "misaligned"])
+def test_two_level_irregular_layouts(B, orc, kind, shape, lanes):  # noqa: F811
+    """Owner tiles of boxes that are no rectilinear grid (the walk of the owner
+    index, neighbours that straddle a face), with every lane count's
+    interleaving of count and histogram blocks."""
+    import dataclasses
+    from test_gpu_parity import irregular_layout, step_vs_oracle
+    w = irregular_layout(seed=17, kind=kind)
+    w = dataclasses.replace(w, cic=repeat_in_boxes(w.cic, 501), sn=repeat_in_boxes(w.sn, 10))
+    assert entries(w) > SMALL_ENTRIES
+    step_vs_oracle(B, orc, w, "fix64", tuning=dict(
+        deposit_path=1, fuse_apply=2, tile_x=shape[0], tile_yz=shape[1], count_lanes=lanes))
+
+
+@pytest.mark.parametrize("lanes", [2, 8])
+@pytest.mark.parametrize("fuse", [0, 1, 2])
+def test_two_level_many_boxes_in_a_block(B, orc, fuse, lanes):  # noqa: F811
+    """Boxes of two to four cells with a few particles each: a block of the sort
+    spans several hundred boxes, more than it stages."""
+    from test_gpu_parity import step_vs_oracle
+    rng = np.random.default_rng(9)
+    edges = [[2, 3, 4] * 6 for _ in range(3)]
+    dom = (54, 54, 54)
+    w = W.multibox(*edges, 2, positions_cic=W.uniform_positions(rng, 20000, dom),
+                   positions_sn=W.uniform_positions(rng, 3000, dom), sn_radius=2.0, seed=6)
+    assert w.nbox > SMALL_TILES and 1024 * w.nbox / w.cic.n > 64
+    step_vs_oracle(B, orc, w, "fix64", tuning=dict(
+        deposit_path=1, fuse_apply=fuse, tile_x=16, tile_yz=4, count_lanes=lanes))
+
+
+def test_two_level_split_tiles_out_of_slots(B, orc):  # noqa: F811
+    """More chunks than chunk slots: the tiles that find no slots stay whole."""
+    from test_gpu_parity import check
+    w = W.c3(nx=128, n_sink=16)
+    assert w.cic.n / 64 > 4 * 256
+    assert padded_tiles((128, 128, 128), w.ghost, 16, 4) > SMALL_TILES
+    check(B, orc, w, "fix64", tuning={"deposit_path": 1, "tile_x": 16, "tile_yz": 4,
+                                      "chunk_cic": 64, "chunk_sn": 16})
+
+
+@pytest.mark.parametrize("nx", [24, 96])
+def test_capacity_drops_only_entries_past_it(B, nx):  # noqa: F811
+    """A caller that declares r_max = 0 for radius-4 supernovae: the entries past
+    the list's end are dropped and flagged, every other one arrives (both
+    sorts: 24^3 has few enough tiles for the short one, 96^3 does not).  Energy:
+    no CIC, and equal shares of every member."""
+    import torch
+    w = W.c2(nx=nx, n_cic=1, n_sn=(nx ** 3) // 168, dtype=np.float64)
+    assert (padded_tiles((nx,) * 3, w.ghost, 16, 2) > SMALL_TILES) == (nx == 96)
+    bufs = []
+    for r_max in (4.0, 0.0):
+        ctx = B.Context(w, "fix64", channels="auto")
+        ctx.set_tuning(deposit_path=1, tile_x=16, tile_yz=2)
+        ctx.sn.r_max = r_max
+        ctx.deposit()
+        torch.cuda.synchronize()
+        st = ctx.status()
+        assert bool(st["flags"] & 0x20) == (r_max == 0.0), st
+        e = ctx.buf.cpu().numpy().reshape(len(ctx.fields), -1)[ctx.fields.index(4)]
+        bufs.append(e.copy())
+        ctx.close()
+    full, cut = bufs
+    # (the remainder cell's share is up to a member count of quanta off)
+    quanta = 1000
+    assert (cut <= full + quanta).all() and (cut >= -quanta).all()
+    kept = cut.astype(np.float64).sum() / full.astype(np.float64).sum()
+    print("kept:", kept, flush=True)
+    assert 0.1 < kept < 0.95, kept
+
+
+def dense(nx=64, n_total=300000):
+    w = W.c4(nx=nx, n_total=n_total)
+    assert entries(w) > SMALL_ENTRIES
+    return w
+
+
+def test_two_level_scratch_grown_by_another_shape(B, orc):  # noqa: F811
+    """A many-tile shape first (the scratch grows to its histograms), then a
+    large-tile one: the launches of the second are sized by its own slices."""
+    import torch
+    from buffers import expand_channels
+    w = dense()
+    ctx = B.Context(w, "fix64")
+    out = []
+    for tx, tyz in ((16, 2), (64, 8), (16, 4)):
+        ctx.set_tuning(deposit_path=1, tile_x=tx, tile_yz=tyz)
+        ctx.deposit()
+        torch.cuda.synchronize()
+        out.append(expand_channels(w, ctx.buf.cpu().numpy().copy(), ctx.fields))
+    st = ctx.status()
+    ctx.close()
+    assert st["flags"] in (0, 0x10), st
+    ref = orc.deposit(w, "fix64")[0]
+    for got in out:
+        assert np.array_equal(got, ref)
+
+
+def test_two_level_launch_shape_invariance(B, orc):  # noqa: F811
+    """The two-level sort gives the oracle's bits whatever the tiles, the launch
+    shape or the lanes per supernova, on ghost-zoned and on owner tiles."""
+    from test_gpu_parity import SHAPES, run_gpu, owner_tiles_fit, step_vs_oracle
+    w = dense()
+    ref = orc.step(w, "fix64")
+    for tun in SHAPES[2:] + [{"deposit_path": 1, "count_lanes": 2},
+                             {"deposit_path": 1, "count_lanes": 8, "tile_x": 16}]:
+        print("tuning", tun, flush=True)
+        got = run_gpu(B, w, "fix64", want_eta=False, tuning=tun)
+        for k in ("buf_deposit", "buf_fold"):
+            assert np.array_equal(got[k], ref[k]), k
+        tx, tyz = tun.get("tile_x", 32), tun.get("tile_yz", 4)
+        if tx <= 32 and owner_tiles_fit(w, tx, tyz):
+            step_vs_oracle(B, orc, w, "fix64", tuning=dict(tun, tile_x=tx, fuse_apply=2))
+
+
+@pytest.mark.parametrize("fuse", [1, 2])
+def test_two_level_workspace_and_graph(B, fuse):  # noqa: F811
+    """Scratch carved from a caller's workspace of the size asked for, eagerly
+    and replayed from a graph with other work in between, gives the library's
+    own scratch's bits."""
+    import torch
+    w = dense()
+    tun = dict(deposit_path=1, tile_x=16, tile_yz=4, fuse_apply=fuse)
+    ref = B.Context(w, "fix64", channels="auto")
+    ref.set_tuning(**tun)
+    ref.step()
+    torch.cuda.synchronize()
+    want = ref.state.cpu().numpy()
+    ctx = B.Context(w, "fix64", channels="auto")
+    ctx.set_tuning(**tun)
+    ctx.set_workspace(torch.full((ctx.workspace_size(),), 0xAB, dtype=torch.uint8, device="cuda"))
+    ctx.step()
+    torch.cuda.synchronize()
+    assert np.array_equal(ctx.state.cpu().numpy(), want)
+    ctx.graph_build(1)
+    for rep in range(3):
+        ctx.reset_state()
+        torch.cuda.synchronize()
+        ctx.graph_launch()
+        torch.cuda.synchronize()
+        assert np.array_equal(ctx.state.cpu().numpy(), want), rep
+        ref.step()
+        torch.cuda.synchronize()
+    ctx.close()
+    ref.close()
+
+
+@pytest.mark.parametrize("dx", [0.5, 0.7])
+@pytest.mark.parametrize("acc", ["fix64", "f64", "f32"])
+@pytest.mark.parametrize("name", ["short", "two_level", "boxes"])
+def test_cell_volumes(B, orc, name, acc, dx):  # noqa: F811
+    """Cell volumes other than one: a power of two, whose exact reciprocal the
+    tile pass multiplies by, and one that it divides by."""
+    import dataclasses
+    from test_gpu_parity import check, step_vs_oracle
+    w = {"short": lambda: W.c2(nx=40), "two_level": dense, "boxes": lambda: W.c5(nb=4)}[name]()
+    w = dataclasses.replace(w, dx=dx, name=f"{w.name}_dx{dx}")
+    check(B, orc, w, acc, tuning={"deposit_path": 1})
+    step_vs_oracle(B, orc, w, acc, tuning=dict(deposit_path=1, fuse_apply=2, tile_x=16))
