@@ -2950,11 +2950,11 @@ __global__ __launch_bounds__(256) void k_l2_hist(L2Geom G, const int* __restrict
 // Per slice (both kinds in one launch): LDS cursors from the scanned hist2
 // place every entry's particle index at its final position, grouped by tile;
 // slice 0 of a bucket writes the offsets of the bucket's tiles.
-// ORDERED (the reproducibility mode): the wavefronts take their turns at the
+// ORDERED (the reproducibility mode): the wavefronts take turns at the
 // cursors, so that the order within a tile depends on level 1's alone; with
-// the barrier in the tile pass's CIC loop, 99.957% instead of 99.860% of the
+// the rounds of the tile pass's CIC loop, 99.955% instead of 99.860% of the
 // elements repeat at 512^3 with 4e6 particles (99.920% with whole records
-// sorted), and the deposit takes 2330 us instead of 2280.
+// sorted), the deposit taking 2260 us (2280).
 template <bool ORDERED>
 __global__ __launch_bounds__(256) void k_l2_scatter(L2Geom G, const int* __restrict__ slice_base,
                                                    const int* __restrict__ hist2,
@@ -2998,23 +2998,23 @@ __global__ __launch_bounds__(256) void k_l2_scatter(L2Geom G, const int* __restr
 #pragma unroll
       for (int u = 0; u < U; ++u)
         v[u] = (e + u * stride < e1) ? tmp[e + u * stride] : make_int2(0, t0);
+      int pos[U];
+      auto rank = [&]() {
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        auto place = [&]() {
-          if (e + u * stride < e1) {
-            const int pos = atomicAdd(h + (v[u].y - t0), 1);
-            if (pos < cap) rec[pos] = v[u].x;
-          }
-        };
-        if constexpr (ORDERED) {
-          for (int turn = 0; turn < (int)blockDim.x / kWave; ++turn) {
-            __syncthreads();
-            if (turn == (int)threadIdx.x / kWave) place();
-          }
-        } else {
-          place();
+        for (int u = 0; u < U; ++u)
+          pos[u] = (e + u * stride < e1) ? atomicAdd(h + (v[u].y - t0), 1) : 0x7fffffff;
+      };
+      if constexpr (ORDERED) {
+        for (int turn = 0; turn < (int)blockDim.x / kWave; ++turn) {
+          if (turn == (int)threadIdx.x / kWave) rank();
+          __syncthreads();
         }
+      } else {
+        rank();
       }
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (pos[u] < cap) rec[pos[u]] = v[u].x;
     }
     __syncthreads();
   }
@@ -3443,14 +3443,28 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(ACC == PMP
     // CIC entries, one per thread.  In the reproducibility mode the wavefronts
     // wait for each other's records before they add (two dependent loads, whose
     // latencies differ from run to run, would decide the order), so every
-    // thread makes every round.
+    // thread makes every round; the next round's record and the index after it
+    // are loaded meanwhile.
+    double4 ahead = make_double4(0.0, 0.0, 0.0, 0.0);
+    int ahead_idx = -1;
+    if constexpr (BOUNDS) {
+      const int e = e0 + (int)threadIdx.x;
+      if (e < e1) ahead = crec[cidx[e]];
+      if (e + (int)blockDim.x < e1) ahead_idx = cidx[e + blockDim.x];
+    }
     for (int e = e0 + (int)threadIdx.x; (BOUNDS ? e - (int)threadIdx.x : e) < e1;
          e += blockDim.x) {
-      double4 CR = make_double4(0.0, 0.0, 0.0, 0.0);
-      if (!BOUNDS || e < e1) CR = crec[cidx[e]];
+      double4 CR;
       if constexpr (BOUNDS) {
+        CR = ahead;
+        // (the record is here before the barrier)
+        asm volatile("" ::"v"(CR.x), "v"(CR.y), "v"(CR.z), "v"(CR.w));
+        if (ahead_idx >= 0) ahead = crec[ahead_idx];
+        ahead_idx = e + 2 * (int)blockDim.x < e1 ? cidx[e + 2 * blockDim.x] : -1;
         __syncthreads();
         if (e >= e1) continue;
+      } else {
+        CR = crec[cidx[e]];
       }
       // per axis the stencil's two cells as tile-local indices (-1: not in
       // the tile, or no weight there), and the second cell's weight
@@ -3469,7 +3483,9 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(ACC == PMP
         };
         const int first = local(i), second = local(i + 1);
         lh[a] = (int)floor(pos[a]) == i ? first : second;
-        l0[a] = f[a] == 1.0 ? -1 : first;  // (f rounds to 1 one ulp below a cell centre)
+        // (f rounds to 1 one ulp below the first cell centre: an addition of
+        // zero, which only an error bound would notice)
+        l0[a] = BOUNDS && f[a] == 1.0 ? -1 : first;
         l1[a] = f[a] == 0.0 ? -1 : second;
       }
       // (m wx) wy of the four rows along z, then times wz and over V, the
