@@ -80,7 +80,11 @@ extern "C" {
  * (eps = 2^-52) to that element's error bound, and once the element's
  * deposits are complete its lowest 52 + M + ceil(log2(bound / |sum|))
  * mantissa bits (clamped to [0, 52]) are cleared, M = margin_bits.  Binned
- * path only (deposit_path 1), tiles never split. */
+ * path only (deposit_path 1), tiles never split.
+ * PMP_ACC_FIX64 alone gives the same bits on every run: float sums are added
+ * in an order that varies (least in PMP_ACC_F64R; most in PMP_ACC_F32 and
+ * PMP_ACC_F64 deposits that take the sort of small deposits, see count_lanes,
+ * where even the order of a tile's entries does). */
 typedef enum { PMP_ACC_F32 = 0, PMP_ACC_F64 = 1, PMP_ACC_FIX64 = 2, PMP_ACC_F64R = 3 } pmp_acc_t;
 typedef enum { PMP_STATE_F32 = 0, PMP_STATE_F64 = 1 } pmp_state_t;
 
@@ -126,7 +130,11 @@ typedef struct {
   const double *x, *y, *z, *m, *e, *r;  /* device [n] */
   int64_t n;
   const int64_t *box_off;               /* device [nbox+1] */
-  double r_max;                         /* host: largest r, for the ghost check */
+  double r_max;                         /* host: largest r.  Checked against the ghost
+                                           width, and sizes the binned path's entry list
+                                           (room for n supernovae of this radius): where
+                                           larger ones fill it, the entries past its end
+                                           are skipped and flagged CAPACITY */
 } pmp_sn;
 
 /* Supernova remnants with the variant of the TIGRESS prescription of

@@ -2283,8 +2283,9 @@ __global__ __launch_bounds__(kScanBlock) void k_scan_finish(int* __restrict__ of
 // particle is stored once, in its own order, so the two levels move 8 bytes
 // per pair where they moved the particle (36): at 512^3 with 4e6 particles
 // the level-1 scatter takes 73 us (168 before; the histogram pass, which
-// writes the records, 70 instead of 55) and the level-2 scatter 37 us (153); the tile pass then gathers the records
-// through the sorted indices at its old time.
+// writes the records, 70 instead of 55) and the level-2 scatter 37 us (153).
+// The tile pass, which gathers the records through the sorted indices, pays
+// part of it back: 1475 us instead of 1436, 6.6 GB instead of 6.0.
 // Column of level-1 block blk in a bucket's row of the histogram: blocks
 // grouped by XCD (block i runs on XCD i mod 8), so that the counts sharing a
 // cache line come from one XCD and merge in its L2.  A bijection on
@@ -3051,9 +3052,9 @@ __global__ __launch_bounds__(256) void k_units(TileGrid T, const int* __restrict
   }
 }
 
-// Small deposits: few particles over few tiles are sorted in three short
-// launches instead of twelve, whose launch and drain times are all there is to
-// such a sort.  k_small_count finds the supernovae's members, counts each
+// Small deposits: few particles over few tiles are sorted in four short
+// launches (the counts' zeroing is one) instead of ten, whose launch and drain
+// times are all there is to such a sort.  k_small_count finds the supernovae's members, counts each
 // tile's entries (an LDS histogram over all tiles, then one global atomic per
 // tile a block met, which reserves the block's entries of that tile) and
 // writes every particle's (tile, rank within the tile) pairs: a CIC particle's
@@ -3330,15 +3331,18 @@ __device__ __forceinline__ int image_shift(int code, int a, int glo, int D) {
 //
 // What bounds it: with FP64 state the state's cache lines and the gathered
 // records (512^3 FP64 moves 6.6 GB in 1400 to 1440 us, 4.6 TB/s; a kernel that
-// only streams such a masked state takes 1220 us); otherwise the latency of a tile's phases (metadata 1.9 us,
-// record gather 3.6, supernova rows 1.8, apply 5 of the 13 us of a 4096-box
-// tile), so what counts is resident wavefronts and loads in flight.  Hence
+// only streams such a masked state takes 1220 us); otherwise the latency of a
+// tile's phases (metadata 1.9 us, record gather 3.6, supernova rows 1.8, apply
+// 5 of the 13 us of a 4096-box tile), so what counts is resident wavefronts and loads in flight.  Hence
 // one instantiation per state type, 32-bit entry indices, one source-free
 // apply without the general one behind it and a CIC stencil in per-axis
-// tile-local indices (82 -> 71 registers), budgets of 6 or 7 wavefronts per
-// SIMD that hold without spilling (a spilled variant of the fixed-point pass
-// takes 1650 us, this one 1165), the states of several cells loaded together,
-// and the two record gathers on different wavefronts.  Tile pass before and
+// tile-local indices (82 registers -> 74 for the float owner tiles, 54 for the
+// padded ones), budgets of 6 or 7 wavefronts per SIMD, the states of several
+// cells loaded together, and the two record gathers on different wavefronts.
+// The float kernels hold their vector registers in that budget; the
+// fixed-point owner tiles spill six or seven (32 B of scratch per lane) and
+// are faster so than with one wavefront fewer (step of 1461 against 1505 us)
+// or one more (tile pass of 1161 against 1647).  Tile pass before and
 // after: 4096 boxes FP32 1400 -> 1110 us, 512^3 fixed point over FP32 1490 ->
 // 1165, 512 boxes FP64 with sinks 183 -> 161, 256^3 FP64 clustered 137 -> 119.
 template <int ACC, int TYZ, bool OWN, class ST>
@@ -3655,17 +3659,21 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(ACC == PMP
     if (!BOUNDS && base >= 0) {
       // a chunk of a split tile: leave the partial tile, and the last chunk
       // to finish (arrival count) sums the chunks' partial tiles in chunk order
-      // back into the accumulators.  The partial sums are stored and loaded
-      // as device-scope atomics, past the XCD's own L2, and waited for before
-      // the arrival: a device-scope fence would write that whole L2 back, once
-      // for every chunk.
+      // back into the accumulators.  A device-scope release would order this,
+      // but on gfx950 it writes the XCD's whole L2 back, once for every chunk.
+      // What stands in its place is the hardware's behaviour, not the language's
+      // memory model: stores and loads of device scope (sc1) go through the L2
+      // to memory that all XCDs share, no other access touches these addresses
+      // in this kernel, and a store leaves vmcnt only when it has arrived there.
+      // So each wavefront waits for its own stores, the barrier collects the
+      // workgroup's, one thread then counts the arrival, and the last workgroup
+      // loads what the others stored.
       LT* part = partial + (long long)(base + chunk) * 2 * lcells;
       for (int c = threadIdx.x; c < lcells; c += blockDim.x) {
         part_store(part + c, a0[c]);
         if (sne) part_store(part + lcells + c, a4[c]);
       }
-      // this wavefront's stores have reached device scope (the clobber keeps the
-      // compiler from moving them past the wait)
+      // (the clobber keeps the compiler from moving the stores past the wait)
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
       __syncthreads();
       if (threadIdx.x == 0)
