@@ -200,7 +200,8 @@ struct alignas(16) SnTile {
 // each pair into its coarse bucket (tile >> shift) through per-block
 // histograms and a global scan; level 2 sorts each bucket by tile and writes
 // the per-tile offsets.  A small deposit's sort uses the same arrays in three
-// kernels (counts per tile in hist2, pair slots in cic_tmp and sn_tmp).
+// kernels (counts per tile in hist2, pairs with their ranks in cic_tmp and
+// sn_tmp).
 struct BinWork {
   int shift;            // coarse bucket = tile >> shift
   int nbuckets;         // ceil(ntiles / 2^shift) <= 1024
